@@ -188,7 +188,7 @@ static bool mfma_pays(const ConvParams& p, bool lean) {
                                                                               : 1.1e12;
   const double t_vec = lean ? pix * p.c_in * p.n_groups / lean_rate + 5e-6
                             : pix * p.n_wt * (p.stride == 2 ? 2.2 : 1.0) / 12e12 + 8e-6;
-  const bool long_k = mfma_long_k(p);
+  const bool long_k = 9 * p.c_in >= 1152;
   const int km = long_k ? 64 : 32;
   const double steps = (9.0 * p.c_in + km - 1) / km;
   const long bm = p.c_out > 64 ? 128 : 64;

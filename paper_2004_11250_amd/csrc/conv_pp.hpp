@@ -197,8 +197,6 @@ bool fewout_eligible(const ConvParams& p);
 hipError_t launch_fewout_conv(const ConvParams& p, bool bf16_act, hipStream_t st);
 bool mfma_eligible(const ConvParams& p);
 size_t mfma_bytes(const ConvParams& p);
-bool mfma_long_k(const ConvParams& p);   // k steps of 64 (else 32)
-int mfma_groups(const ConvParams& p);    // wave groups per tile splitting its k steps (1 or 2)
 hipError_t launch_mfma_conv(const ConvParams& p, hipStream_t st);   // PP_PREPARED in p.flags: no expansion
 hipError_t launch_mfma_expand(const ConvParams& p, void* out, hipStream_t st);   // the weights into out
 

@@ -14,20 +14,17 @@
 // idle; the planner picks per layer.
 //
 // Each call expands the blob into A in the caller's scratch
-// (pp_mfma_expand_kernel: original filter order, k = (tap, channel), channel
-// fastest, and the bias in original order) and runs an implicit GEMM
-// C[o][pixel] = sum_k A[o][k] B[k][pixel], with B the input gathered on the
-// fly (never stored).  k advances 32 or 64 at a time; with c_in a multiple
-// of 32 the k of a step that one thread gathers for its pixel are one tap of
-// consecutive channels, which differ only by the channel stride, taken as the
-// loads' scalar offset.  Products of
-// bf16 values are exact in fp32; sums are fp32; the epilogue (bias, ReLU,
-// accumulate, PixelShuffle(2)) rounds once to bf16, as the vector kernels do.
+// (pp_mfma_expand_kernel: original filter order, in the matrix cores' operand
+// order, and the bias in original order) and runs an implicit GEMM
+// C[o][pixel] = sum_k A[o][k] B[k][pixel], with B read from the staged input
+// (never stored).  Products of bf16 values are exact in fp32; sums are fp32;
+// the epilogue (bias, ReLU, accumulate, PixelShuffle(2)) rounds once to bf16,
+// as the vector kernels do.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 
-#include "conv_pp.hpp"
+#include "conv_pp_kernel.hpp"
 
 namespace pp {
 namespace {
@@ -35,17 +32,24 @@ namespace {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
+struct MTiles {
+  uint32_t m_tiles, tiles_x, tiles_y;
+};
+
 constexpr uint32_t kOut = 0x80000000u;   // byte offset of an element outside a tensor (reads zero)
 
-__device__ __forceinline__ uint32_t rne_bf16(float v) {
-  uint32_t u = __float_as_uint(v);
-  u += 0x7FFFu + ((u >> 16) & 1u);   // round to nearest even (finite values)
-  return u >> 16;
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// lo and hi in bf16, rounded to nearest even
+__device__ __forceinline__ uint32_t cvt_bf16x2(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
 }
-__device__ __forceinline__ float bf16_val(uint32_t u) { return __uint_as_float(u << 16); }
+__device__ __forceinline__ float bf16_val(uint32_t u) { return __uint_as_float(u << 16); }   // of the low half
+__device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
 
 // One thread per (slot group g, slot s, input channel c), channel fastest:
-// the 9 taps of kernel (perm[8 g + s], c) into A[o][t][c] (zeros for taps off
+// the 9 taps of kernel (perm[8 g + s], c) into A (zeros for taps off
 // the pattern and for pruned kernels), and the slot's bias into bo[o].  Every
 // (filter, channel) pair is written exactly once.  Offsets read from the
 // device blob are clamped (a pattern id past the library reads as pruned, a
@@ -74,240 +78,319 @@ __global__ __launch_bounds__(256) void pp_mfma_expand_kernel(ConvParams a, uint1
   for (int q = 0; q < s; ++q) idx += (static_cast<uint32_t>(__builtin_popcount(mask_of(q))) + 1u) & ~1u;
   const uint32_t m = mask_of(s);
   const uint16_t* w = reinterpret_cast<const uint16_t*>(a.blob + a.off_w);
-  uint16_t* dst = am + static_cast<size_t>(o) * 9 * a.c_in + c;
+  // operand order (see pp_mfma_conv_kernel): blocks of 32 filters, each [16 channels][tap][half][row][8 channels]
+  const uint32_t mb = o >> 5, rows = min(32u, static_cast<uint32_t>(a.c_out) - 32u * mb);
+  uint16_t* dst = am + static_cast<size_t>(mb) * 32 * 9 * a.c_in +
+                  ((static_cast<size_t>(c >> 4) * 18 + ((c >> 3) & 1)) * rows + (o & 31)) * 8 + (c & 7);
   for (int t = 0; t < 9; ++t) {
     uint16_t v = 0;
     if ((m >> t) & 1u) {
       v = idx < a.n_wt ? w[idx] : static_cast<uint16_t>(0);
       ++idx;
     }
-    dst[static_cast<size_t>(t) * a.c_in] = v;
+    dst[static_cast<size_t>(t) * 16 * rows] = v;
   }
   if (c == 0) bo[o] = reinterpret_cast<const float*>(a.blob + a.off_bias)[gs];
 }
 
-// Workgroup: 4 waves as 2 x 2, each wave TM x TN blocks of 32 x 32 of C: a
-// tile is BM = 64 TM filters by BN = 64 TN pixels.  Two LDS buffers, row-major
-// with k contiguous ([m][k], [n][k]), so each lane's MFMA operand (8
-// consecutive k of one row) is one 16-byte read; the next step's global loads
-// are in registers while the matrix cores run this one.  A: each thread loads
-// 16-byte pieces of rows; B: each thread gathers KPT consecutive channels of
-// one pixel (lanes take consecutive pixels, so each load is coalesced).  UP: the
-// conv's input is the nearest x2 upsampling of x (PP_UPSAMPLE2).
-template <int TM, int TN, int KM, bool UP, int G>
-__global__ __launch_bounds__(256 * G) void pp_mfma_conv_kernel(ConvParams a, const uint16_t* __restrict__ am,
-                                                               const float* __restrict__ bias, int n_tiles) {
-  constexpr int BM = 64 * TM, BN = 64 * TN;
-  constexpr int kMK = KM;               // k per step: KM / 16 MFMAs per block
-  constexpr int kPitch = kMK + 8;       // LDS row pitch in bf16 (80 or 144 bytes: a lane's 16-byte reads spread over the banks)
-  constexpr int KPT = kMK * BN / 256;   // B elements per thread per step
-  constexpr int APR = kMK / 8;          // 16-byte A pieces per row and step
-  constexpr int JA = BM * APR / 256;    // A pieces per thread
-  static_assert(KPT % 8 == 0 && 32 % KPT == 0, "a thread's channels of a step are one tap (c_in a multiple of 32)");
-  // per wave group: two buffers of A (BM rows) and B (BN rows); after the
-  // loop the space holds the second group's accumulators
-  constexpr int kRows = BM + BN;
-  __shared__ __attribute__((aligned(16))) uint16_t smem[G * 2 * kRows * kPitch];
-  static_assert(G == 1 || sizeof(smem) >= TM * TN * 16 * 256 * sizeof(float), "room for the group reduction");
-  const int tid = threadIdx.x & 255, lane = tid & 63;
-  const int grp = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 8));
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  auto As = [&](int buf, int row, int col) __attribute__((always_inline)) {
-    return &smem[((grp * 2 + buf) * kRows + row) * kPitch + col];
-  };
-  auto Bs = [&](int buf, int row, int col) __attribute__((always_inline)) {
-    return &smem[((grp * 2 + buf) * kRows + BM + row) * kPitch + col];
-  };
-  const int wm = wv & 1, wn = wv >> 1;
-  const int nt = static_cast<int>(blockIdx.x % static_cast<uint32_t>(n_tiles));
-  const int mt = static_cast<int>(blockIdx.x / static_cast<uint32_t>(n_tiles));
-  const int K = 9 * a.c_in;
-  const int steps = (K + kMK - 1) / kMK;   // K is a multiple of 32: the last step may be half
-  const long np = static_cast<long>(a.n) * a.ho * a.wo;
-  const int hs = UP ? a.h / 2 : a.h, wsd = UP ? a.w / 2 : a.w;   // stored input size
-  const uint32_t hw = static_cast<uint32_t>(hs) * wsd;
+// lgkmcnt(0), then the workgroup barrier: LDS traffic is complete, global
+// loads stay in flight across it
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
 
-  // A: rows ar + (256 / APR) j, k 8 aq .. 8 aq + 7 of the step
-  const int ar = tid / APR, aq = tid % APR;
-  const __amdgpu_buffer_rsrc_t arsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(am), static_cast<short>(0), a.c_out * K * 2, 0x00020000);
-  uint32_t aoff[JA];
-#pragma unroll
-  for (int j = 0; j < JA; ++j) {
-    const int row = mt * BM + ar + (256 / APR) * j;
-    aoff[j] = row < a.c_out ? (static_cast<uint32_t>(row) * K + 8 * aq) * 2 : kOut;
+// Tile geometry.  A workgroup is 4 waves, WM along the filters and 4 / WM
+// along the pixels; a wave owns 64 filters (2 blocks of 32) by TN blocks of
+// 32 pixels.  The pixel tile is TH x TW outputs of one image; its input halo
+// (HR x HC) is staged CB channels at a time as [pixel][channel], PITCH bytes
+// a pixel (16 more than the channels need: neighbouring pixels' 16-byte
+// pieces then fall on different banks).
+template <int WM, int TN, int CB, int TW_, int S, int D>
+struct MGeo {
+  static constexpr int WN = 4 / WM, BM = 64 * WM, NBLK = WN * TN, BN = 32 * NBLK;
+  static constexpr int TW = TW_, TH = BN / TW, RPB = 32 / TW;   // rows of a 32-pixel block
+  static constexpr int HR = (TH - 1) * S + 2 * D + 1;
+  static constexpr int HC = ((TW - 1) * S + 2 * D + 1 + 1 + 1) / 2 * 2;   // from an even column: one more, even
+  static constexpr int PITCH = 2 * CB + 16;
+  static constexpr int BUF = HR * HC * PITCH;                  // bytes of one staged block
+  static constexpr int LDS = 2 * BUF;
+};
+
+// What bounds it and why this form: the contraction needs 9 c_in k per
+// output, and gathering B per tap from NCHW (2-byte loads, one per element
+// and tap) was bound by the load instructions.  Here a channel block's halo
+// is read from memory once, transposed in registers (8 channels of a pixel
+// pair: eight 4-byte loads, eight byte permutes, two 16-byte LDS writes) and
+// read by all nine taps as shifted 16-byte LDS reads.  The weights never
+// touch LDS: they lie in memory in operand order (one contiguous KB per 32
+// filters x 16 k), so each operand is one coalesced 16-byte load per lane,
+// issued PF k-steps ahead; k runs channel block by channel block of 16, tap
+// by tap inside.  Measured (bf16, us, per-tap gather -> this): 64 -> 64 at
+// 270 x 480 37 -> 19, 64 -> 256 at 540 x 960 with the shuffle 317 -> 170,
+// 512 -> 512 on 8 x 32 x 32 62 -> 39 (dilation 2 83 -> 37): 35-40 % of the
+// 2.5 PFLOP/s peak on the large ones, 0.8-1.0 of what a large library
+// matrix product reaches on the card (1.15).  What is left is the weights'
+// way through each unit's cache (a tile half as large takes 1.4x), and on
+// small grids the wait for each channel block's input.
+// PX2: the halo is staged by pixel pairs (even image width, no upsample),
+// else pixel by pixel; with PP_UPSAMPLE2 the conv's input is the nearest x2
+// upsampling of x.
+template <int WM, int TN, int CB, int TW_, int S, int D, bool PX2>
+__global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, const uint16_t* __restrict__ am,
+                                                               const float* __restrict__ bias, MTiles mt) {
+  using M = MGeo<WM, TN, CB, TW_, S, D>;
+  constexpr int KS = CB / 16 * 9;        // k-steps (16 deep) of a channel block
+  constexpr int PF = TN < 4 && KS % 6 == 0 ? 6 : 3;   // weights in flight ahead, in k-steps (divides KS)
+  constexpr int PW = PX2 ? 2 : 1;        // pixels per staged item
+  constexpr int NPC = M::HC / PW;        // items across
+  constexpr int ITEMS = NPC * M::HR * (CB / 8);
+  constexpr int NIT = (ITEMS + 255) / 256;
+  __shared__ __attribute__((aligned(16))) uint8_t smem[M::LDS];
+  __shared__ float bias_s[M::BM];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wv % WM, wn = wv / WM;
+
+  // block -> (image, tile, filter tile): filter tiles of one pixel tile are neighbours on one XCD
+  uint32_t blk = kern::xcd_remap(blockIdx.x, gridDim.x);
+  const uint32_t mtile = blk % mt.m_tiles;
+  blk /= mt.m_tiles;
+  const uint32_t txi = blk % mt.tiles_x;
+  blk /= mt.tiles_x;
+  const uint32_t tyi = blk % mt.tiles_y;
+  const uint32_t img = blk / mt.tiles_y;
+  const int oy0 = tyi * M::TH, ox0 = txi * M::TW;
+  const int iy0 = oy0 * S - a.pad, ixw = ox0 * S - a.pad;
+  const int ix0 = ixw & ~1, sh = ixw & 1;   // the staged columns start at an even one
+
+  for (int i = tid; i < M::BM; i += 256) {
+    const int o = mtile * M::BM + i;
+    bias_s[i] = o < a.c_out ? bias[o] : 0.0f;
   }
-  // B: pixel bn, channels kb .. kb + KPT - 1 of the step (kb is wave-uniform)
-  const int bn = tid % BN;
-  const int kb = __builtin_amdgcn_readfirstlane(tid / BN) * KPT;
-  const long bp = static_cast<long>(nt) * BN + bn;
-  const bool bvalid = bp < np;
-  int oy = 0, ox = 0;
-  long img = 0;
-  if (bvalid) {
-    ox = static_cast<int>(bp % a.wo);
-    const long q = bp / a.wo;
-    oy = static_cast<int>(q % a.ho);
-    img = q / a.ho;
-  }
-  const uint32_t ximg = static_cast<uint32_t>(img) * a.c_in * hw;
+
+  // input: per-item byte offsets within a channel block (kOut: outside the image)
+  const bool up = !PX2 && (a.flags & PP_UPSAMPLE2) != 0;
+  const int hs = up ? a.h / 2 : a.h, wsd = up ? a.w / 2 : a.w;   // stored input size
+  const uint32_t hw = static_cast<uint32_t>(hs) * wsd;
   const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void*>(a.x), static_cast<short>(0), static_cast<int>(static_cast<uint32_t>(a.n) * a.c_in * hw * 2),
       0x00020000);
-
-  uint32_t ra[JA][4], rb[KPT];
-  auto fetch = [&](int st) __attribute__((always_inline)) {
-    const int k0 = st * kMK;
-    // a thread's KPT channels are one tap (c_in is a multiple of KPT); k
-    // past K (the second half of a half step) reads zero
-    const int t = (k0 + kb) / a.c_in, c0 = k0 + kb - t * a.c_in;
-    const int ky = t / 3, kx = t - 3 * ky;
-    const bool a_in = k0 + 8 * aq < K;
+  uint32_t xoff[NIT], loff[NIT];
 #pragma unroll
-    for (int j = 0; j < JA; ++j) {
-      const auto v =
-          __builtin_amdgcn_raw_buffer_load_b128(arsrc, aoff[j] == kOut || !a_in ? kOut : aoff[j] + 2 * k0, 0, 0);
-      ra[j][0] = v[0];
-      ra[j][1] = v[1];
-      ra[j][2] = v[2];
-      ra[j][3] = v[3];
-    }
-    uint32_t bo = kOut;
-    if (bvalid && k0 + kb < K) {
-      const int iy = oy * a.stride + ky * a.dil - a.pad, ix = ox * a.stride + kx * a.dil - a.pad;
-      if (iy >= 0 && iy < a.h && ix >= 0 && ix < a.w) {
-        const int sy = UP ? iy >> 1 : iy, sx = UP ? ix >> 1 : ix;
-        bo = (ximg + static_cast<uint32_t>(sy) * wsd + sx) * 2;
+  for (int t = 0; t < NIT; ++t) {
+    const int e = tid + 256 * t;
+    const int pc = e % NPC, q = e / NPC, hr = q % M::HR, oct = q / M::HR;
+    const int gy = iy0 + hr, gx = ix0 + PW * pc;
+    const bool ok = e < ITEMS && gy >= 0 && gy < a.h && gx >= 0 && gx < a.w;
+    const uint32_t el = up ? static_cast<uint32_t>(gy >> 1) * wsd + (gx >> 1) : static_cast<uint32_t>(gy) * wsd + gx;
+    xoff[t] = ok ? (static_cast<uint32_t>(img) * a.c_in * hw + 8u * oct * hw + el) * 2u : kOut;
+    // items past the tile's last write over its first pixels' padding bytes (nobody reads those)
+    loff[t] = e < ITEMS ? (hr * M::HC + PW * pc) * M::PITCH + 16 * oct : 2 * CB;
+  }
+  uint32_t rb[NIT][8];
+  auto fetch = [&](int cb) __attribute__((always_inline)) {
+    const uint32_t c2 = static_cast<uint32_t>(cb) * CB * hw * 2u;
+#pragma unroll
+    for (int t = 0; t < NIT; ++t)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        if constexpr (PX2)
+          rb[t][j] = __builtin_amdgcn_raw_buffer_load_b32(xrsrc, xoff[t], static_cast<int>(c2 + j * hw * 2u), 0);
+        else
+          rb[t][j] = __builtin_amdgcn_raw_buffer_load_b16(xrsrc, xoff[t], static_cast<int>(c2 + j * hw * 2u), 0);
       }
-    }
-#pragma unroll
-    for (int j = 0; j < KPT; ++j)
-      rb[j] = __builtin_amdgcn_raw_buffer_load_b16(xrsrc, bo, static_cast<int>((c0 + j) * hw * 2), 0);
   };
   auto put = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < JA; ++j) {
-      uint32_t* d = reinterpret_cast<uint32_t*>(As(buf, ar + (256 / APR) * j, 8 * aq));
-      *reinterpret_cast<uint4*>(d) = make_uint4(ra[j][0], ra[j][1], ra[j][2], ra[j][3]);
-    }
+    for (int t = 0; t < NIT; ++t) {
+      uint8_t* d = smem + buf * M::BUF + loff[t];
+      uint32_t lo[4], hi[4];
 #pragma unroll
-    for (int q = 0; q < KPT / 8; ++q) {
-      uint32_t* d = reinterpret_cast<uint32_t*>(Bs(buf, bn, kb + 8 * q));
-      *reinterpret_cast<uint4*>(d) =
-          make_uint4((rb[8 * q] & 0xFFFFu) | (rb[8 * q + 1] << 16), (rb[8 * q + 2] & 0xFFFFu) | (rb[8 * q + 3] << 16),
-                     (rb[8 * q + 4] & 0xFFFFu) | (rb[8 * q + 5] << 16), (rb[8 * q + 6] & 0xFFFFu) | (rb[8 * q + 7] << 16));
+      for (int k = 0; k < 4; ++k) {
+        lo[k] = __builtin_amdgcn_perm(rb[t][2 * k + 1], rb[t][2 * k], 0x05040100u);
+        hi[k] = __builtin_amdgcn_perm(rb[t][2 * k + 1], rb[t][2 * k], 0x07060302u);
+      }
+      *reinterpret_cast<uint4*>(d) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+      if constexpr (PX2) {
+        if ((t + 1) * 256 <= ITEMS || tid + 256 * t < ITEMS)
+          *reinterpret_cast<uint4*>(d + M::PITCH) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+      }
     }
   };
 
-  f32x16 acc[TM][TN];
+  // weights: block of 32 filters mb holds, per k-step, [half][row][8 k] of its
+  // R = min(32, c_out - 32 mb) rows; a row past them reads zero
+  const __amdgpu_buffer_rsrc_t arsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(am), static_cast<short>(0), a.c_out * 9 * a.c_in * 2, 0x00020000);
+  uint32_t aoff[2], astep[2];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < 2; ++i) {
+    const int mb = mtile * (M::BM / 32) + wm * 2 + i;
+    const int rows = min(32, a.c_out - 32 * mb);
+    const int row = lane & 31;
+    aoff[i] = row < rows ? static_cast<uint32_t>(mb) * 32u * 18u * a.c_in + ((lane >> 5) * rows + row) * 16u : kOut;
+    astep[i] = rows > 0 ? 32u * rows : 0u;
+  }
+  const int nblk = a.c_in / CB;
+  const uint32_t last_step = static_cast<uint32_t>(nblk) * KS - 1;
+  typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+  u32x4v ar[PF][2];
+  auto load_a = [&](int slot, uint32_t step) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      ar[slot][i] = __builtin_bit_cast(
+          u32x4v, __builtin_amdgcn_raw_buffer_load_b128(arsrc, aoff[i], static_cast<int>(step * astep[i]), 0));
+  };
+
+  // pixel operands: this lane's pixel of the wave's first block, tap (0, 0)
+  const int lp = lane & 31;
+  const int prow = wn * TN * M::RPB + lp / M::TW, pcol = lp % M::TW;
+  const uint32_t lbase = (prow * S * M::HC + pcol * S + sh) * M::PITCH + (lane >> 5) * 16;
+
+  f32x16 acc[2][TN];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x16{};
-  // wave group g takes k steps g, g + G, g + 2 G, ...: G tiles' worth of
-  // loads in flight per workgroup; every thread runs every iteration (and
-  // barrier), a group without a step that iteration only waits
-  const int iters = (steps + G - 1) / G;
-  if (grp < steps) {
-    fetch(grp);
-    put(0);
-  }
-  __syncthreads();
-  for (int it = 0; it < iters; ++it) {
-    const int buf = it & 1;
-    const int s = it * G + grp;
-    if (s + G < steps) fetch(s + G);
-    if (s < steps) {
-      // a 32 x 32 x 16 MFMA takes row l % 32 of A and column l % 32 of B, k
-      // 8 (l / 32) .. 8 (l / 32) + 7 of its 16, in lane l
+
+  fetch(0);
 #pragma unroll
-      for (int h = 0; h < kMK; h += 16) {
-        bf16x8 av[TM], bv[TN];
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-          av[i] = *reinterpret_cast<const bf16x8*>(As(buf, (wm * TM + i) * 32 + (lane & 31), h + 8 * (lane >> 5)));
+  for (int s = 0; s < PF; ++s) load_a(s, s);
+  put(0);
+  lds_barrier();
+#pragma unroll 1
+  for (int cb = 0; cb < nblk; ++cb) {
+    const bool more = cb + 1 < nblk;
+    {
+      const uint8_t* bsrc = smem + (cb & 1) * M::BUF + lbase;
+      auto read_b = [&](int s, bf16x8 (&bv)[TN]) __attribute__((always_inline)) {
+        const int h = s / 9, t = s % 9, ky = t / 3, kx = t % 3;
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-          bv[j] = *reinterpret_cast<const bf16x8*>(Bs(buf, (wn * TN + j) * 32 + (lane & 31), h + 8 * (lane >> 5)));
+          bv[j] = *reinterpret_cast<const bf16x8*>(bsrc + ((ky * D + j * M::RPB * S) * M::HC + kx * D) * M::PITCH + h * 32);
+      };
+      bf16x8 bv[2][TN];
+      read_b(0, bv[0]);
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+      for (int s = 0; s < KS; ++s) {
+        // (loads return in order: issued any earlier, the next block's input would hold up the weights behind it)
+        if (s == KS - PF && more) fetch(cb + 1);
+        if (s + 1 < KS) read_b(s + 1, bv[(s + 1) & 1]);
+        bf16x8 av[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) av[i] = __builtin_bit_cast(bf16x8, ar[s % PF][i]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
           for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bv[j], acc[i][j], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bv[s & 1][j], acc[i][j], 0, 0, 0);
+        // the ring's next k-step (past the last one that one again: nothing outside the weights is read)
+        const int ns = s + PF;
+        load_a(s % PF, min(static_cast<uint32_t>(cb * KS + ns), last_step));
+        // (left to itself the scheduler sinks the weight loads to their use, a step's wait each)
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if (s + G < steps) put(buf ^ 1);   // that buffer's last readers passed the barrier below one iteration ago
-    __syncthreads();
-  }
-  if constexpr (G == 2) {
-    // group 1's sums into group 0's (one fixed order), through LDS (the
-    // operand buffers are dead: every wave passed the last barrier)
-    float* red = reinterpret_cast<float*>(smem);
-    if (grp == 1) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) red[((i * TN + j) * 16 + r) * 256 + tid] = acc[i][j][r];
-    }
-    __syncthreads();
-    if (grp == 1) return;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] += red[((i * TN + j) * 16 + r) * 256 + tid];
+    if (more) put((cb & 1) ^ 1);   // that buffer's last readers passed the previous barrier
+    lds_barrier();
   }
 
-  // accumulator r of block (i, j), lane l, is C[8 (r / 4) + 4 (l / 32) + r % 4][l % 32] of the block
-  const bool relu = (a.flags & PP_RELU) != 0, accum = (a.flags & PP_ACCUMULATE) != 0;
-  const bool shuf = (a.flags & PP_PIXSHUF2) != 0;
+  // accumulator r of block (i, j), lane l, is C[8 (r / 4) + 4 (l / 32) + r % 4][l % 32] of the block.
+  // A row's address is a wave-uniform base (filter 8 (r / 4) + r % 4) plus a
+  // 32-bit lane offset (4 filters for the upper half of the wave, and the pixel).
+  const bool relu = (a.flags & PP_RELU) != 0;
+  const int ex = ox0 + pcol;
+  const size_t plane = static_cast<size_t>(a.ho) * a.wo;
+  uint16_t* __restrict__ y = static_cast<uint16_t*>(a.y) + static_cast<size_t>(img) * a.c_out * plane;
+  const uint32_t half4 = (lane >> 5) * 4, odd = lane & 1;
+  const int ob = mtile * M::BM + wm * 64;   // the wave's first filter
+  auto act2 = [&](int i, int j, int r) __attribute__((always_inline)) -> uint32_t {   // rows r, r + 1, in bf16
+    const int ol = (wm * 2 + i) * 32 + 8 * (r >> 2) + half4 + (r & 3);
+    float v0 = acc[i][j][r] + bias_s[ol], v1 = acc[i][j][r + 1] + bias_s[ol + 1];
+    if (relu) {
+      v0 = fmaxf(v0, 0.0f);
+      v1 = fmaxf(v1, 0.0f);
+    }
+    return cvt_bf16x2(v0, v1);
+  };
+  if (a.flags & PP_PIXSHUF2) {
+    // PixelShuffle(2): filters o, o + 1 (o even; accumulators r, r + 1)
+    // land in adjacent columns 2 ex, 2 ex + 1 of one output row: one
+    // 4-byte store per pair (c_out is a multiple of 4)
 #pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const long gp = static_cast<long>(nt) * BN + (wn * TN + j) * 32 + (lane & 31);
-    if (gp >= np) continue;
-    const int ex = static_cast<int>(gp % a.wo);
-    const long q = gp / a.wo;
-    const int ey = static_cast<int>(q % a.ho);
-    const long eimg = q / a.ho;
-    uint16_t* __restrict__ y = static_cast<uint16_t*>(a.y) + static_cast<size_t>(eimg) * a.c_out * a.ho * a.wo;
-    if (shuf && !accum) {
-      // PixelShuffle(2): filters o, o + 1 (o even; accumulators r, r + 1)
-      // land in adjacent columns 2 ex, 2 ex + 1 of one output row: one
-      // aligned 4-byte store per pair (c_out is a multiple of 4)
+    for (int j = 0; j < TN; ++j) {
+      const int ey = oy0 + prow + j * M::RPB;
+      if (ey >= a.ho || ex >= a.wo) continue;
+      const uint32_t voff = (half4 * static_cast<uint32_t>(plane) + (2u * ey) * 2u * a.wo + 2u * ex) * 2u;
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int r = 0; r < 16; r += 2) {
-          const int o = mt * BM + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          if (o < a.c_out) {
-            float v0 = acc[i][j][r] + bias[o], v1 = acc[i][j][r + 1] + bias[o + 1];
-            if (relu) {
-              v0 = fmaxf(v0, 0.0f);
-              v1 = fmaxf(v1, 0.0f);
-            }
-            const size_t at = (static_cast<size_t>(o >> 2) * 2 * a.ho + 2 * ey + ((o >> 1) & 1)) * 2 * a.wo + 2 * ex;
-            *reinterpret_cast<uint32_t*>(y + at) = rne_bf16(v0) | (rne_bf16(v1) << 16);
-          }
+          const int os = ob + 32 * i + 8 * (r >> 2);   // multiple of 8
+          uint8_t* row = reinterpret_cast<uint8_t*>(y + static_cast<size_t>(os) * plane + (r & 2) * a.wo);
+          if (os + static_cast<int>(half4) < a.c_out) *reinterpret_cast<uint32_t*>(row + voff) = act2(i, j, r);
         }
-      continue;
     }
+    return;
+  }
+  const bool accum = (a.flags & PP_ACCUMULATE) != 0;
+  if (a.wo % 2 == 0 && reinterpret_cast<uintptr_t>(a.y) % 4 == 0) {
+    // columns in pairs: an even lane stores filter o of its and its
+    // neighbour's pixel, the neighbour filter o + 1 of both (4-byte stores)
+    const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int j = 0; j < TN; ++j) {
+      const int ey = oy0 + prow + j * M::RPB;
+      const bool valid = ey < a.ho && ex < a.wo;
+      const uint32_t voff = ((half4 + odd) * static_cast<uint32_t>(plane) + static_cast<uint32_t>(ey) * a.wo + ex - odd) * 2u;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int o = mt * BM + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (o < a.c_out) {
-          float v = acc[i][j][r] + bias[o];
-          if (relu) v = fmaxf(v, 0.0f);
-          const size_t at = shuf ? (static_cast<size_t>(o >> 2) * 2 * a.ho + 2 * ey + ((o >> 1) & 1)) * 2 * a.wo +
-                                       2 * ex + (o & 1)
-                                 : (static_cast<size_t>(o) * a.ho + ey) * a.wo + ex;
+      for (int i = 0; i < 2; ++i) {
+        auto at = [&](int r) __attribute__((always_inline)) {
+          return reinterpret_cast<uint32_t*>(
+              reinterpret_cast<uint8_t*>(y + static_cast<size_t>(ob + 32 * i + 8 * (r >> 2) + (r & 3)) * plane) + voff);
+        };
+        auto in = [&](int r) __attribute__((always_inline)) {
+          return valid && ob + 32 * i + 8 * (r >> 2) + (r & 3) + static_cast<int>(half4 + odd) < a.c_out;
+        };
+        uint32_t old[8];
+        if (accum) {
+#pragma unroll
+          for (int r = 0; r < 16; r += 2) old[r / 2] = in(r) ? *at(r) : 0u;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+          const uint32_t u = act2(i, j, r);
+          const uint32_t nb = __builtin_amdgcn_mov_dpp(u, 0xB1, 0xF, 0xF, true);   // lanes 1, 0, 3, 2 of each four
+          uint32_t t = __builtin_amdgcn_perm(nb, u, sel);
           // PP_ACCUMULATE: y = y + act(...), the activated value rounded to bf16 first
-          const float t = accum ? bf16_val(y[at]) + bf16_val(rne_bf16(v)) : v;
-          y[at] = static_cast<uint16_t>(rne_bf16(t));
+          if (accum)
+            t = cvt_bf16x2(bf16_val(old[r / 2]) + bf16_val(t), bf16_hi(old[r / 2]) + bf16_hi(t));
+          if (in(r)) *at(r) = t;
+        }
+      }
+    }
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int ey = oy0 + prow + j * M::RPB;
+    if (ey >= a.ho || ex >= a.wo) continue;
+    const uint32_t voff = (half4 * static_cast<uint32_t>(plane) + static_cast<uint32_t>(ey) * a.wo + ex) * 2u;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) {
+        const uint32_t u = act2(i, j, r);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const int os = ob + 32 * i + 8 * (r >> 2) + (r & 3) + k;
+          if (os + static_cast<int>(half4) >= a.c_out) break;
+          uint16_t* d = reinterpret_cast<uint16_t*>(reinterpret_cast<uint8_t*>(y + static_cast<size_t>(os) * plane) + voff);
+          const uint32_t b = k ? u >> 16 : u & 0xFFFFu;
+          *d = static_cast<uint16_t>(accum ? cvt_bf16x2(bf16_val(*d) + bf16_val(b), 0.0f) : b);
         }
       }
   }
@@ -317,30 +400,35 @@ size_t a_bytes(const ConvParams& p) {
   return (static_cast<size_t>(p.c_out) * 9 * p.c_in * 2 + 255) / 256 * 256;
 }
 
-template <int TM, int TN, int KM, bool UP>
+// workgroups of a layer in tiles of bm filters x (th x tw) outputs
+long tiles(const ConvParams& p, int bm, int th, int tw) {
+  return static_cast<long>((p.c_out + bm - 1) / bm) * ((p.ho + th - 1) / th) * ((p.wo + tw - 1) / tw) * p.n;
+}
+
+template <int WM, int TN, int CB, int TW, int S, int D>
 hipError_t launch_tiles(const ConvParams& p, const uint16_t* am, const float* bo, hipStream_t st) {
-  constexpr int BM = 64 * TM, BN = 64 * TN;
-  const long np = static_cast<long>(p.n) * p.ho * p.wo;
-  const long n_tiles = (np + BN - 1) / BN, m_tiles = (p.c_out + BM - 1) / BM;
-  const long blocks = n_tiles * m_tiles;
-  if (blocks < 1 || blocks > 0x7FFFFFFFL) return hipErrorInvalidConfiguration;
+  using M = MGeo<WM, TN, CB, TW, S, D>;
+  static_assert(M::LDS + M::BM * 4 <= 160 * 1024, "staging buffers fit the LDS");
+  MTiles t;
+  t.m_tiles = (p.c_out + M::BM - 1) / M::BM;
+  t.tiles_x = (p.wo + M::TW - 1) / M::TW;
+  t.tiles_y = (p.ho + M::TH - 1) / M::TH;
+  const size_t blocks = static_cast<size_t>(t.m_tiles) * t.tiles_x * t.tiles_y * p.n;
+  if (blocks < 1 || blocks > 0x7FFFFFFFu) return hipErrorInvalidConfiguration;
   const dim3 grid(static_cast<uint32_t>(blocks));
-  // grids of at most one tile per compute unit: two wave groups per tile
-  // splitting its k steps (twice the loads in flight; with 512 tiles, whose
-  // 8-wave workgroups no longer all fit at once, it timed slower)
-  if (mfma_groups(p) == 2)
-    hipLaunchKernelGGL((pp_mfma_conv_kernel<TM, TN, KM, UP, 2>), grid, dim3(512), 0, st, p, am, bo,
-                       static_cast<int>(n_tiles));
+  // pixel pairs: rows of whole 4-byte words (an upsampled input reads each stored pixel twice)
+  const bool px2 = p.w % 2 == 0 && !(p.flags & PP_UPSAMPLE2) && reinterpret_cast<uintptr_t>(p.x) % 4 == 0;
+  if (px2)
+    hipLaunchKernelGGL((pp_mfma_conv_kernel<WM, TN, CB, TW, S, D, true>), grid, dim3(256), 0, st, p, am, bo, t);
   else
-    hipLaunchKernelGGL((pp_mfma_conv_kernel<TM, TN, KM, UP, 1>), grid, dim3(256), 0, st, p, am, bo,
-                       static_cast<int>(n_tiles));
+    hipLaunchKernelGGL((pp_mfma_conv_kernel<WM, TN, CB, TW, S, D, false>), grid, dim3(256), 0, st, p, am, bo, t);
   return hipGetLastError();
 }
 
 }  // namespace
 
 bool mfma_eligible(const ConvParams& p) {
-  if (p.c_in < 32 || p.c_in % 32 != 0 || p.c_out < 1) return false;   // (KPT = 32 channels)
+  if (p.c_in < 32 || p.c_in % 32 != 0 || p.c_out < 1) return false;   // (staged 32 channels at a time)
   if (p.flags & PP_MAXPOOL2) return false;
   if (p.stride < 1 || p.stride > 2 || p.dil < 1 || p.dil > 2 || p.pad < 0) return false;
   const bool up = (p.flags & PP_UPSAMPLE2) != 0;
@@ -350,14 +438,6 @@ bool mfma_eligible(const ConvParams& p) {
   const size_t hw = static_cast<size_t>(up ? p.h / 2 : p.h) * (up ? p.w / 2 : p.w);
   return static_cast<size_t>(p.n) * p.c_in * hw * 2 < (size_t{1} << 30) &&
          static_cast<size_t>(p.c_out) * 9 * p.c_in * 2 < (size_t{1} << 30);
-}
-
-bool mfma_long_k(const ConvParams& p) { return 9 * p.c_in >= 1152; }
-
-int mfma_groups(const ConvParams& p) {
-  const long bm = p.c_out > 64 ? 128 : 64;
-  const long tiles = (static_cast<long>(p.n) * p.ho * p.wo + 127) / 128 * ((p.c_out + bm - 1) / bm);
-  return tiles <= 256 ? 2 : 1;
 }
 
 size_t mfma_bytes(const ConvParams& p) { return a_bytes(p) + static_cast<size_t>(p.c_out) * sizeof(float); }
@@ -380,18 +460,37 @@ hipError_t launch_mfma_conv(const ConvParams& p, hipStream_t st) {
     const hipError_t e = launch_mfma_expand(p, p.part, st);
     if (e != hipSuccess) return e;
   }
-  const bool up = (p.flags & PP_UPSAMPLE2) != 0;
-  // 128 x 128 tiles for more than 64 filters, else 64 x 128; k steps of 64
-  // for reductions of 1152+ (fewer, longer steps: better where each tile's
-  // long reduction is latency-bound), else 32 (half the LDS: more tiles per
-  // compute unit) -- timed on the super-resolution, style-transfer and
-  // colourization layers
-  if (mfma_long_k(p)) {
-    if (p.c_out > 64) return up ? launch_tiles<2, 2, 64, true>(p, am, bo, st) : launch_tiles<2, 2, 64, false>(p, am, bo, st);
-    return up ? launch_tiles<1, 2, 64, true>(p, am, bo, st) : launch_tiles<1, 2, 64, false>(p, am, bo, st);
+  // Tiles (filters x pixels; timed on MI355X, bf16, us): the weights cross
+  // each compute unit's caches once per wave, so larger tiles are better as
+  // long as every unit still gets one or two workgroups.
+  //   128 x 256 from 512 such tiles (64 -> 256 at 270 x 480: 44, 128 x 128 47;
+  //     512 -> 512 on 8 x 32 x 32, 128 tiles: 60 against 37)
+  //   128 x 128 from 192 (that layer; 128 -> 256 on 8 x 64 x 64: 23, 64 x 128 33)
+  //   64 x 256 for at most 64 filters from 400 (64 -> 64 at 270 x 480: 18, 64 x 128 21)
+  //   64 x 128 below (128 -> 128 at 128 x 128: 12.3, 128 x 128 14)
+  // 128 x 128 stages 64 channels at a time when c_in is a multiple of 64 (one workgroup per
+  // unit: half the waits for a block's input; 512 -> 512: 37 against 39).  The
+  // 128-pixel tiles are 4 x 32 or 8 x 16 outputs, whichever covers the map with fewer tiles.
+  // Every tile sums in the same order: the choice never changes a result's bits.
+  const bool wide = p.c_out > 64, d1 = p.dil == 1;
+  if (p.stride == 2) {
+    if (!d1) return launch_tiles<1, 1, 16, 32, 2, 2>(p, am, bo, st);
+    if (wide && tiles(p, 128, 4, 32) >= 192) return launch_tiles<2, 2, 32, 32, 2, 1>(p, am, bo, st);
+    return launch_tiles<1, 1, 16, 32, 2, 1>(p, am, bo, st);
   }
-  if (p.c_out > 64) return up ? launch_tiles<2, 2, 32, true>(p, am, bo, st) : launch_tiles<2, 2, 32, false>(p, am, bo, st);
-  return up ? launch_tiles<1, 2, 32, true>(p, am, bo, st) : launch_tiles<1, 2, 32, false>(p, am, bo, st);
+  if (d1 && wide && tiles(p, 128, 8, 32) >= 512) return launch_tiles<2, 4, 32, 32, 1, 1>(p, am, bo, st);
+  if (d1 && !wide && tiles(p, 64, 8, 32) >= 400) return launch_tiles<1, 2, 32, 32, 1, 1>(p, am, bo, st);
+  const bool tall = tiles(p, 128, 8, 16) < tiles(p, 128, 4, 32);   // 8 x 16 covers the map with fewer
+  if (wide && tiles(p, 128, tall ? 8 : 4, tall ? 16 : 32) >= 192) {
+    if (p.c_in % 64 == 0) {
+      if (tall) return d1 ? launch_tiles<2, 2, 64, 16, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 64, 16, 1, 2>(p, am, bo, st);
+      return d1 ? launch_tiles<2, 2, 64, 32, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 64, 32, 1, 2>(p, am, bo, st);
+    }
+    if (tall) return d1 ? launch_tiles<2, 2, 32, 16, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 32, 16, 1, 2>(p, am, bo, st);
+    return d1 ? launch_tiles<2, 2, 32, 32, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 32, 32, 1, 2>(p, am, bo, st);
+  }
+  if (tall) return d1 ? launch_tiles<1, 1, 32, 16, 1, 1>(p, am, bo, st) : launch_tiles<1, 1, 32, 16, 1, 2>(p, am, bo, st);
+  return d1 ? launch_tiles<1, 1, 32, 32, 1, 1>(p, am, bo, st) : launch_tiles<1, 1, 32, 32, 1, 2>(p, am, bo, st);
 }
 
 }  // namespace pp

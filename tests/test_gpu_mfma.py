@@ -246,3 +246,41 @@ def test_prepared_weights_ignored_off_the_matrix_cores():
     got = _host(pp.conv2d_fwd(layer, x, relu=True, prepared=True))
     assert np.array_equal(got, want)
     assert torch.equal(buf, before)
+
+
+# each tile of the matrix-core form at its edges: ragged rows and columns,
+# odd widths (staged pixel by pixel), 8 x 16 tiles, and an input that starts
+# on an odd 2-byte element (no 4-byte loads)
+TILES = [  # (stride, dilation), (n, c_out, c_in, h, w)
+    ((1, 1), (2, 72, 32, 198, 330)),     # 128 filters x 256 pixels
+    ((1, 1), (2, 72, 32, 198, 329)),
+    ((1, 1), (1, 40, 64, 199, 498)),     # 64 x 256
+    ((1, 1), (1, 33, 32, 199, 497)),
+    ((1, 1), (8, 128, 64, 63, 40)),      # 128 x 128 as 8 x 16, 64 channels at a time
+    ((1, 2), (8, 127, 96, 62, 39)),      # as 8 x 16, 32 at a time
+    ((1, 1), (4, 100, 96, 94, 64)),      # as 4 x 32, 32 at a time
+    ((1, 2), (4, 100, 64, 94, 63)),
+    ((2, 1), (4, 130, 32, 191, 127)),    # stride 2, 128 x 128
+    ((1, 1), (1, 34, 32, 9, 14)),        # 64 x 128 as 8 x 16
+    ((1, 2), (1, 34, 32, 9, 13)),
+]
+
+
+@pytest.mark.parametrize("case", range(len(TILES)))
+def test_mfma_tiles(case, monkeypatch):
+    monkeypatch.setenv("PP_RECIPE", str(MFMA))
+    (s, d), (n, c_out, c_in, h, w) = TILES[case]
+    seed = 1700 + case
+    L, layer = _layer(seed, c_out, c_in, "canon8", 0.5, s, d, d)
+    x = obf16.round_f32(workloads.random_input(seed, (n, c_in, h, w)))
+    _say("mfma tiles", (s, d), (n, c_out, c_in, h, w), "seed", seed)
+    assert pp.conv2d_recipe(layer.h_blob, n, h, w, pp.PP_BF16) == MFMA
+    xd = _dev(x)
+    yd = pp.conv2d_fwd(layer, xd, relu=True)
+    sel = np.unique([0, c_out // 2, c_out - 1])
+    ref, bound = _oracle(L, x, s, d, d, True, sel)
+    check(_host(yd)[:, sel], ref, bound, "bf16", f"mfma tiles {TILES[case]}")
+    off = torch.empty(xd.numel() + 1, dtype=xd.dtype, device="cuda")[1:].view(xd.shape)
+    off.copy_(xd)
+    assert off.data_ptr() % 4 == 2
+    assert torch.equal(pp.conv2d_fwd(layer, off, relu=True), yd)   # same sums, other loads
