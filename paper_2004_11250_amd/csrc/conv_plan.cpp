@@ -80,6 +80,14 @@ static bool recipe_usable(int id, const ConvParams& p, int lib, bool bf16) {
   return !is_wave_recipe(id) || p.pad == p.dil;
 }
 
+bool gen_usable(int id, const ConvParams& p, bool bf16) {
+  if (p.stride != 1 || p.dil != 1 || p.pad != 1 || (p.flags & ~static_cast<uint32_t>(PP_RELU))) return false;
+  if (bf16 && p.w % 2) return false;   // (its staging moves whole dwords)
+  const bool v4 = id == 66 || id == 68;
+  // (a plan query has no x: its launch checks the address)
+  return !v4 || (p.w % (bf16 ? 8 : 4) == 0 && reinterpret_cast<uintptr_t>(p.x) % 16 == 0);
+}
+
 static int env_recipe() {
   const char* e = std::getenv("PP_RECIPE");
   if (!e || !*e) return -1;
@@ -244,6 +252,19 @@ ConvPlan plan_conv(const ConvParams& p, int lib, bool bf16, bool allow_split, bo
       mfma_pays(p, lean_layer && bf16 && p.w % 2 == 0 && !(p.flags & (PP_UPSAMPLE2 | PP_PIXSHUF2))))
     return mfma;
   const long pix = static_cast<long>(p.ho) * p.wo;
+  if (lib == kLibGeneric && !no_lean && p.c_in > 8) {
+    // any other library: the mask-testing lean kernel, 2 x 4 outputs per lane
+    // with 8 waves, on small maps 2 x 2 with 16 (column-pruned, fp32:
+    // 128 -> 128 at 128 x 128 55 us, 2 x 2 82, 176 on the channel-chunk
+    // kernel; 64 -> 64 at 100 x 100 19, 26, 96, at 40 x 40 18, 13, 63)
+    const bool small = pix < 64L * 64L;
+    ConvPlan pl;
+    for (int id : {small ? 68 : 66, small ? 69 : 67, forced})
+      if ((forced < 0 || forced == id) && is_gen_recipe(id) && gen_usable(id, p, bf16)) {
+        pl.recipe = id;
+        return pl;
+      }
+  }
   if (lean_layer) {
     // fp32, stride 1: the lean tilings that timed fastest on the
     // VGG-16 layer shapes (MI355X), by output size: 4 x 4 outputs per lane on
@@ -421,6 +442,7 @@ hipError_t launch_conv(int lib, const ConvPlan& plan, const ConvParams& p0, bool
   p.ksplit = plan.ksplit;
   if (plan.ksplit > 1 && !is_wave_recipe(plan.recipe) && !is_lean_recipe(plan.recipe))
     return hipErrorInvalidConfiguration;
+  if (is_gen_recipe(plan.recipe)) return launch_lean_recipe(plan.recipe, p, bf16_act, st);
   if (!recipe_usable(plan.recipe, p, lib, bf16_act)) return hipErrorInvalidConfiguration;
   if (is_lean_recipe(plan.recipe)) return launch_lean_recipe(plan.recipe, p, bf16_act, st);
   if (is_wave_recipe(plan.recipe)) {

@@ -113,6 +113,16 @@ constexpr int kFirstWaveRecipe = 20;
   X(58, 2, 4, 8, 16, 1) \
   X(59, 2, 4, 8, 16, 0)
 
+// Tilings of the lean kernel's mask-testing form (any pattern library): id,
+// R x CC outputs per lane (8 lanes across), WS channel-split waves, 16-byte staging.
+#define PP_GRECIPES(X)     \
+  X(66, 2, 4, 8, true)     \
+  X(67, 2, 4, 8, false)    \
+  X(68, 2, 2, 16, true)    \
+  X(69, 2, 2, 16, false)
+constexpr int kFirstGenRecipe = 66;
+constexpr int kEndGenRecipe = 70;
+
 constexpr int kFirstLeanRecipe = 40;
 constexpr int kEndLeanRecipe = 60;
 
@@ -224,6 +234,11 @@ hipError_t launch_wave_recipe(int id, const ConvParams& p, hipStream_t st);
 
 // lean kernel (conv_pp_lean.hip)
 inline bool is_lean_recipe(int id) { return id >= kFirstLeanRecipe && id < kEndLeanRecipe; }
+inline bool is_gen_recipe(int id) { return id >= kFirstGenRecipe && id < kEndGenRecipe; }
+// whether the mask-testing form can run a layer in tiling id (fp32 or bf16;
+// stride, dilation and pad 1, no fused epilogue other than ReLU; 16-byte
+// staging: width and input aligned to it)
+bool gen_usable(int id, const ConvParams& p, bool bf16);
 hipError_t launch_lean_recipe(int id, const ConvParams& p, bool bf16_act, hipStream_t st);
 // LDS bytes of a lean tiling for fp32 or bf16 activations at stride 1 and
 // dilation (= pad) 1, or fp32 at dilation 2 or stride 2 (0: not compiled

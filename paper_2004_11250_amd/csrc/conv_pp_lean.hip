@@ -42,6 +42,11 @@ hipError_t launch_lean_recipe(int id, const ConvParams& c, bool bf16, hipStream_
   p.wprep = static_cast<const uint8_t*>(c.wprep);
   const bool pw = c.wprep != nullptr;
   p.groups = make_fastdiv(c.n_groups);
+  if (is_gen_recipe(id)) {
+    p.off_masks = c.off_masks;
+    p.n_patterns = static_cast<uint32_t>(c.n_patterns);
+    return gen_usable(id, c, bf16) ? launch_lean_gen(id, p, c.n, bf16, st) : hipErrorInvalidConfiguration;
+  }
   // (stride, dilation = pad): (1, 1); fp32 also (1, 2) and (2, 1)
   const bool ok = c.pad == c.dil && ((c.stride == 1 && c.dil == 1) ||
                                      (!bf16 && ((c.stride == 1 && c.dil == 2) || (c.stride == 2 && c.dil == 1))));

@@ -61,6 +61,7 @@ struct LeanParams {
   uint32_t h = 0, w = 0, ho = 0, wo = 0;
   uint32_t c_in = 0, c_out = 0;
   uint32_t off_codes = 0, off_woff = 0, off_w = 0, off_bias = 0, off_perm = 0, blob_bytes = 0;
+  uint32_t off_masks = 0, n_patterns = 0;   // (GEN)
   uint32_t flags = 0;
   uint32_t ksplit = 1;
   const uint8_t* wprep = nullptr;   // prepared weights (PW): [groups][c_in][32] fp32
@@ -78,7 +79,9 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv& f) {
 // for bf16).  Sizes below are in elements unless named otherwise.
 // D: the dilation (= the padding): 1, or 2 for fp32; S: the stride: 1, or 2
 // for fp32 at dilation 1.
-template <int R, int CC, int LW, int WS, bool V4, bool BF = false, int D = 1, int S = 1>
+// GEN: any pattern library (the mask-testing form): a channel's stored weights
+// are staged as they lie in the blob (up to 72 floats, or 80 bf16 in pairs)
+template <int R, int CC, int LW, int WS, bool V4, bool BF = false, int D = 1, int S = 1, bool GEN = false>
 struct LGeo {
   static_assert(D == 1 || (D == 2 && !BF), "dilation 2: fp32 only");
   static_assert(S == 1 || (S == 2 && !BF && D == 1), "stride 2: fp32 at dilation 1 only");
@@ -104,12 +107,16 @@ struct LGeo {
   static constexpr int EPD = DPB / ES;                   // elements per DMA instruction
   static constexpr int NQ = (AREA + EPD - 1) / EPD;      // DMAs per lane and channel
   static constexpr int PATCH = NQ * DPB / 4;             // 4-byte words of a staged channel
-  static constexpr int SLOT = PATCH + 64;                // + 8 slots x 4 expanded weights (padded)
+  static constexpr int NWD = GEN && !BF ? 2 : 1;         // weight DMAs per channel
+  static constexpr int SLOT = PATCH + 64 * NWD;          // + 8 slots x 4 expanded weights (padded), or the stored ones
   // ring of NS channels (a channel's DMA is issued NS - 1 channels ahead);
   // the smaller rings when four slots would leave a CU fewer than two
   // workgroups of 8 waves, and two slots when three would not fit one
   // workgroup's LDS
-  static constexpr int NS = (WS * 4 * SLOT * 4 <= 80 * 1024) ? 4 : (WS * 3 * SLOT * 4 <= 160 * 1024) ? 3 : 2;
+  // (GEN, whose channel steps are several times longer: two workgroups per CU come first)
+  static constexpr int NS = (WS * 4 * SLOT * 4 <= 80 * 1024)                    ? 4
+                            : (WS * 3 * SLOT * 4 <= (GEN ? 80 : 160) * 1024) ? 3
+                                                                                : 2;
   static constexpr int RING = NS * SLOT;
   static constexpr int NACC = 8 * R * CC;
   // partial-sum exchange: SPP slots per pass, as many as fit the LDS that
@@ -163,9 +170,17 @@ __device__ __forceinline__ void read_row_bf(float (&d)[PC], const uint8_t* rb) {
 // 32 at the end of the step before it), each kept slot's 4 copied to VGPRs
 // for its FMAs: no weight DMA and no LDS reads of weights, which relieves the
 // LDS path the patch DMAs and reads share
-template <int R, int CC, int LW, int WS, bool V4, bool BF = false, bool PW = false, int D = 1, int S = 1>
+// GEN: any pattern library.  The library's masks sit in two registers (two
+// masks per lane) and a channel's stored weights in one or two (one dword per
+// lane), both read with v_readlane.  Column pruning gives a channel the same
+// mask in every filter: its 9 tap tests then serve all 8 slots, so a step is
+// nearly all FMAs (VALU-bound: 128 -> 128 at 128 x 128, half the columns kept,
+// fp32, 55 us = 44 TFLOP/s against 176 on the channel-chunk kernel); any other
+// channel tests each kept slot's taps in turn.
+template <int R, int CC, int LW, int WS, bool V4, bool BF = false, bool PW = false, int D = 1, int S = 1, bool GEN = false>
 __global__ __launch_bounds__(WS * 64) void pp_conv3x3_lean_kernel(LeanParams a) {
-  using G = LGeo<R, CC, LW, WS, V4, BF, D, S>;
+  using G = LGeo<R, CC, LW, WS, V4, BF, D, S, GEN>;
+  static_assert(!(GEN && PW), "prepared weights: canonical library only");
   constexpr uint32_t ES = G::ES;
   constexpr int PR = G::PR, PC = G::PC, LSTR = G::LSTR, NQ = G::NQ, SLOT = G::SLOT, NS = G::NS;
   static_assert(G::fits, "tiling does not fit");
@@ -261,6 +276,16 @@ __global__ __launch_bounds__(WS * 64) void pp_conv3x3_lean_kernel(LeanParams a) 
   auto dma_weights = [&](uint32_t wo, uint32_t sb, bool live) __attribute__((always_inline)) {
     u32x4 d = brs;
     d.z = live ? brs.z : 0u;
+    if constexpr (GEN) {
+      // the dwords from the channel's first weight on (past the blob: zeros)
+      const uint32_t o = a.off_w + ES * (wo & 0xFFFFFFu) + 4u * lane + kDmaShift;
+      static_for<0, G::NWD>([&](auto ti) __attribute__((always_inline)) {
+        constexpr uint32_t L = LW0 + 256u * decltype(ti)::value;
+        dma_b32_at<L, decltype(ti)::value ? L - 256u : static_cast<uint32_t>(G::DPB) * (NQ - 1), false>(
+            d, o + 256u * decltype(ti)::value - (L & 4095u), sb);
+      });
+      return;
+    }
     const uint32_t kept = wo >> 24;
     const uint32_t o = wbase + ES * ((wo & 0xFFFFFFu) + 4u * __builtin_popcount(kept & wlow));
     dma_b32_at<LW0, static_cast<uint32_t>(G::DPB) * (NQ - 1), false>(d, (kept & wbit) ? o : 0x80000000u, sb);
@@ -282,6 +307,14 @@ __global__ __launch_bounds__(WS * 64) void pp_conv3x3_lean_kernel(LeanParams a) 
   const uint32_t pslot = grp * 8 + (lane & 7);
   const uint32_t perm_l = *reinterpret_cast<const uint32_t*>(blob + a.off_perm + 4u * pslot);
   const float bias_l = *reinterpret_cast<const float*>(blob + a.off_bias + 4u * pslot);
+  // GEN: masks 2 lane, 2 lane + 1 of the library's first 128 and of the rest
+  uint32_t mreg[2] = {0u, 0u};
+  if constexpr (GEN) {
+    const uint32_t last = (a.n_patterns - 1u) / 2u;
+#pragma unroll
+    for (uint32_t i = 0; i < 2; ++i)
+      mreg[i] = *reinterpret_cast<const uint32_t*>(blob + a.off_masks + 4u * min(64u * i + lane, last));
+  }
   __builtin_amdgcn_sched_barrier(0);
 
   float acc[8][R][CC];
@@ -292,7 +325,7 @@ __global__ __launch_bounds__(WS * 64) void pp_conv3x3_lean_kernel(LeanParams a) 
 #pragma unroll
       for (int qq = 0; qq < CC; ++qq) acc[s][r][qq] = 0.0f;
   if (c0 < c1) {
-    constexpr int QV = NQ + (PW ? 0 : 1);   // DMAs per lane and channel
+    constexpr int QV = NQ + (PW ? 0 : G::NWD);   // DMAs per lane and channel
     constexpr int DPF = NS - 1;  // channels DMA'd ahead
     constexpr uint32_t SLOTB = 4u * SLOT;
     // ring slots (LDS byte addresses): rd holds channel c, and channel c +
@@ -345,10 +378,15 @@ __global__ __launch_bounds__(WS * 64) void pp_conv3x3_lean_kernel(LeanParams a) 
       const float4* wc = reinterpret_cast<const float4*>(cur + G::PATCH);
       float w[4][4];
       uint32_t wq[16];   // bf16: the 8 slots' taps as pairs
+      uint32_t wv[2] = {0u, 0u};   // GEN: the channel's stored weights, a dword per lane
+      if constexpr (GEN) {
+#pragma unroll
+        for (int i = 0; i < G::NWD; ++i) wv[i] = reinterpret_cast<const uint32_t*>(cur + G::PATCH)[64 * i + lane];
+      }
       float p[PR][PC];
       {
         if constexpr (BF) {
-          if constexpr (!PW) {
+          if constexpr (!PW && !GEN) {
             const uint4* wu = reinterpret_cast<const uint4*>(cur + G::PATCH);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -360,7 +398,7 @@ __global__ __launch_bounds__(WS * 64) void pp_conv3x3_lean_kernel(LeanParams a) 
 #pragma unroll
           for (int r = 0; r < PR; ++r) read_row_bf<PC, CC % 4 == 0>(p[r], pb + r * LSTR * ES);
         } else {
-          if constexpr (!PW) {
+          if constexpr (!PW && !GEN) {
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
               const float4 v = wc[s];
@@ -403,7 +441,65 @@ __global__ __launch_bounds__(WS * 64) void pp_conv3x3_lean_kernel(LeanParams a) 
       asm volatile("" : "+s"(kc));   // fresh slot tests
       {
         const uint32_t cx = code_c.x, cy = code_c.y;
-        if constexpr (PW) {
+        if constexpr (GEN) {
+          (void)w;
+          (void)wq;
+          (void)wc;
+          auto mask_of = [&](uint32_t code) __attribute__((always_inline)) -> uint32_t {
+            const uint32_t i = (code >> 1) & 63u;
+            const uint32_t u = code & 128u ? __builtin_amdgcn_readlane(mreg[1], i) : __builtin_amdgcn_readlane(mreg[0], i);
+            return (code & 1u ? u >> 16 : u) & 0x1FFu;
+          };
+          // stored weight idx of the channel (only slot 7's can lie past the 64th dword)
+          auto stored = [&](uint32_t idx, bool slot7) __attribute__((always_inline)) -> uint32_t {
+            if constexpr (BF) {
+              const uint32_t u = __builtin_amdgcn_readlane(wv[0], (idx >> 1) & 63u);
+              return idx & 1u ? u & 0xFFFF0000u : u << 16;
+            }
+            return slot7 && idx >= 64u ? __builtin_amdgcn_readlane(wv[1], idx & 63u) : __builtin_amdgcn_readlane(wv[0], idx & 63u);
+          };
+          // into a VGPR (an SGPR operand would halve the FMA rate)
+          auto to_vgpr = [&](uint32_t u) __attribute__((always_inline)) -> float {
+            float f;
+            asm volatile("v_mov_b32 %0, %1" : "=v"(f) : "s"(u));
+            return f;
+          };
+          if (kc == 0xFFu && cx == cy && cx == (cx & 0xFFu) * 0x01010101u) {
+            uint32_t m = mask_of(cx & 0xFFu);
+            const uint32_t k = __builtin_popcount(m), ks8 = BF ? (k + 1u) & ~1u : k;   // (bf16 kernels: an even count)
+            uint32_t j = 0;
+            static_for<0, 9>([&](auto ti) __attribute__((always_inline)) {
+              constexpr int T = decltype(ti)::value;
+              if (sbit<T>(m)) {
+                // (the 8 reads first: each takes a few cycles to reach the FMAs)
+                uint32_t u[8];
+                float f[8];
+#pragma unroll
+                for (int s = 0; s < 8; ++s) u[s] = stored(j + s * ks8, s == 7);
+#pragma unroll
+                for (int s = 0; s < 8; ++s) f[s] = to_vgpr(u[s]);
+#pragma unroll
+                for (int s = 0; s < 8; ++s) fma_tap<T, S, D>(acc[s], p, f[s]);
+                ++j;
+              }
+            });
+          } else {
+            uint32_t j = 0;
+            static_for<0, 8>([&](auto si) __attribute__((always_inline)) {
+              constexpr int s = decltype(si)::value;
+              if (!((kc >> s) & 1u)) return;
+              uint32_t m = mask_of(((s < 4 ? cx : cy) >> (8 * (s & 3))) & 0xFFu);
+              static_for<0, 9>([&](auto ti) __attribute__((always_inline)) {
+                constexpr int T = decltype(ti)::value;
+                if (sbit<T>(m)) {
+                  fma_tap<T, S, D>(acc[s], p, to_vgpr(stored(j, s == 7)));
+                  ++j;
+                }
+              });
+              if constexpr (BF) j = (j + 1u) & ~1u;
+            });
+          }
+        } else if constexpr (PW) {
           (void)w;
           (void)wq;
           static_for<0, 8>([&](auto si) __attribute__((always_inline)) {
@@ -766,9 +862,9 @@ __global__ __launch_bounds__(256) void pp_lean_reduce_kernel(LeanParams a) {
 }
 
 #ifndef __HIPCC_RTC__   // host side
-template <int R, int CC, int LW, int WS, bool V4, bool BF = false, bool PW = false, int D = 1, int S = 1>
+template <int R, int CC, int LW, int WS, bool V4, bool BF = false, bool PW = false, int D = 1, int S = 1, bool GEN = false>
 hipError_t launch_lean_tiling(LeanParams p, int n, hipStream_t st) {
-  using G = LGeo<R, CC, LW, WS, V4, BF, D, S>;
+  using G = LGeo<R, CC, LW, WS, V4, BF, D, S, GEN>;
   if constexpr (!G::fits) {
     return hipErrorInvalidConfiguration;
   } else {
@@ -786,7 +882,7 @@ hipError_t launch_lean_tiling(LeanParams p, int n, hipStream_t st) {
     const size_t nb = static_cast<size_t>(ng) * p.ksplit * tx * ty * n;
     if (nb == 0 || nb > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
     if (PW && !p.wprep) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((pp_conv3x3_lean_kernel<R, CC, LW, WS, V4, BF, PW, D, S>), dim3(static_cast<uint32_t>(nb)),
+    hipLaunchKernelGGL((pp_conv3x3_lean_kernel<R, CC, LW, WS, V4, BF, PW, D, S, GEN>), dim3(static_cast<uint32_t>(nb)),
                        dim3(WS * 64), 0, st, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.ksplit == 1) return e;
@@ -805,6 +901,8 @@ hipError_t launch_lean_tiling(LeanParams p, int n, hipStream_t st) {
 // or does not fit)
 hipError_t launch_lean_d2(int id, const LeanParams& p, int n, bool pw, hipStream_t st);
 long lean_lds_bytes_d2(int id);
+// the tilings of the mask-testing form (conv_pp_lean_gen.hip)
+hipError_t launch_lean_gen(int id, const LeanParams& p, int n, bool bf16, hipStream_t st);
 hipError_t launch_lean_s2(int id, const LeanParams& p, int n, bool pw, hipStream_t st);
 long lean_lds_bytes_s2(int id);
 #endif
