@@ -241,8 +241,14 @@ ConvPlan plan_conv(const ConvParams& p, int lib, bool bf16, bool allow_split, bo
     if (pl.recipe >= 0) return pl;
   }
   if (cin_ok && forced < 0) return cin;
-  // (bf16: 64 -> 3 at 1080 x 1920 228 -> 135 us; fp32 stays on the wave kernel, 173 against 186 here)
-  if (few_any && lib == kLibDense9 && bf16 && forced < 0) return few;
+  // (64 -> 3 at 1080 x 1920: bf16 111 us, 228 on the wave kernel; fp32 138
+  // against 172 there, 800 x 1280 60 against 82, 540 x 960 42 against 41.
+  // fp32 only with every kernel kept: a pruned one's zero taps would meet
+  // infinities here, which the wave kernel never reads.)
+  if (few_any && lib == kLibDense9 && forced < 0 &&
+      (bf16 || (p.n == 1 && p.c_out <= 4 && static_cast<long>(p.h) * p.w >= 960L * 1024 &&
+                p.n_wt == 9u * static_cast<uint32_t>(p.c_in) * p.c_out)))
+    return few;
   // (dilation 2 = pad 2, or stride 2: fp32 only)
   const bool lean_layer = lib == kLibCanon8 && p.pad == p.dil &&
                           ((p.stride == 1 && p.dil == 1) ||

@@ -12,9 +12,13 @@
 // a pruned layer does dense work -- the planner takes this kernel for the
 // all-ones library), and each wave then walks the input channels with no
 // dispatch at all: per channel it loads its lanes' input rows straight from
-// global memory one channel ahead (each input element reaches the chip
-// once; halo overlap between neighbouring lanes hits the caches) and does
-// NF x 9 taps x 8 outputs of FMAs per lane, weights read from LDS.
+// global memory two channels ahead and does NF x 9 taps x 8 outputs of FMAs
+// per lane, weights read from LDS.  The columns beside a lane's four come from
+// its neighbours by DPP: loading them too asked the caches for every line
+// three times, and that, not memory, bound the kernel.  64 -> 3 at
+// 1080 x 1920: fp32 190 -> 144 us (3.9 TB/s), bf16 134 -> 111 us.  Even and odd
+// channels have sums of their own (fp32 error against 64 bits 2.7e-7 -> 1.8e-7
+// of the result, the wave kernel's 2.0e-7).
 //
 // Tile: a wave covers 64 x 8 outputs (16 lanes across x 4 down, a 2 x 4
 // block per lane); a workgroup is 4 waves stacked vertically (64 x 32).
@@ -22,12 +26,13 @@
 
 #include <cstdint>
 
-#include "conv_pp.hpp"
+#include "conv_pp_kernel.hpp"
 
 namespace pp {
 namespace kern {
 
 constexpr int kFewTW = 64, kFewTH = 32;   // workgroup tile (4 waves of 64 x 8)
+constexpr int kFewAhead = 2;               // channels in flight (even: odd and even ones have sums of their own)
 constexpr int kFewLds = 60 * 1024;        // bytes of the expanded weight table at most
 
 template <int NF>
@@ -42,7 +47,7 @@ __device__ __forceinline__ uint32_t few_bf16(float f) {   // round to nearest ev
 }
 
 template <int NF, class TA>
-__global__ __launch_bounds__(256) void pp_conv3x3_fewout_kernel(ConvParams a) {
+__global__ __launch_bounds__(256, NF == 8 ? 2 : NF == 4 ? 3 : 4) void pp_conv3x3_fewout_kernel(ConvParams a) {
   constexpr int WPC = FewGeo<NF>::WPC;
   constexpr bool BF = sizeof(TA) == 2;
   extern __shared__ __attribute__((aligned(16))) float wtab[];   // [c_in][WPC]
@@ -52,7 +57,8 @@ __global__ __launch_bounds__(256) void pp_conv3x3_fewout_kernel(ConvParams a) {
   const int lane = tid & 63;
   const int wk = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tiles_x = a.tiles_x, tiles_y = a.tiles_y;
-  int blk = blockIdx.x;
+  // neighbouring tiles (which share halo cache lines) on one XCD
+  int blk = static_cast<int>(xcd_remap(blockIdx.x, gridDim.x));
   const int tx = blk % tiles_x;
   blk /= tiles_x;
   const int ty = blk % tiles_y;
@@ -111,51 +117,69 @@ __global__ __launch_bounds__(256) void pp_conv3x3_fewout_kernel(ConvParams a) {
   // channel.
   constexpr uint32_t kOut = 0x80000000u;
   constexpr uint32_t ES = sizeof(TA);
-  uint32_t om[4], ol[4], orr[4];
+  uint32_t om[4], oe[4];   // the lane's 4 columns; the column beside them, for the outer lanes of the 16
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int gy = oy - 1 + r;
     const bool rv = lane_in && gy >= 0 && gy < a.h;
     const uint32_t base = static_cast<uint32_t>(gy * a.w + ox) * ES;
     om[r] = rv ? base : kOut;
-    ol[r] = rv && ox > 0 ? base - ES : kOut;
-    orr[r] = rv && ox + 4 < a.w ? base + 4 * ES : kOut;
+    oe[r] = rv && lx == 0 && ox > 0 ? base - ES : rv && lx == 15 && ox + 4 < a.w ? base + 4 * ES : kOut;
   }
   const TA* x = static_cast<const TA*>(a.x) + static_cast<size_t>(img) * a.c_in * cstride;
   const int chan_bytes = static_cast<int>(cstride * ES);
-  auto load_patch = [&](int c, float (&pt)[4][6]) __attribute__((always_inline)) {
+  // a channel's rows as loaded (widened when they are used: a conversion
+  // right behind the loads would wait for them there)
+  constexpr int NW = BF ? 2 : 4;
+  struct Rows {
+    uint32_t v[4][NW], e[4];
+  };
+  auto load_rows = [&](int c, Rows& p) __attribute__((always_inline)) {
     const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<TA*>(x + static_cast<size_t>(c) * cstride), static_cast<short>(0), chan_bytes, 0x00020000);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       if constexpr (BF) {
-        const uint2 u = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(xr, om[r], 0, 0));
-        pt[r][1] = __uint_as_float(u.x << 16); pt[r][2] = __uint_as_float(u.x & 0xFFFF0000u);
-        pt[r][3] = __uint_as_float(u.y << 16); pt[r][4] = __uint_as_float(u.y & 0xFFFF0000u);
-        pt[r][0] = __uint_as_float(static_cast<uint32_t>(__builtin_amdgcn_raw_buffer_load_b16(xr, ol[r], 0, 0)) << 16);
-        pt[r][5] = __uint_as_float(static_cast<uint32_t>(__builtin_amdgcn_raw_buffer_load_b16(xr, orr[r], 0, 0)) << 16);
+        const auto u = __builtin_amdgcn_raw_buffer_load_b64(xr, om[r], 0, 0);
+        p.v[r][0] = u[0]; p.v[r][1] = u[1];
+        p.e[r] = __builtin_amdgcn_raw_buffer_load_b16(xr, oe[r], 0, 0);
       } else {
-        const float4 u = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(xr, om[r], 0, 0));
-        pt[r][1] = u.x; pt[r][2] = u.y; pt[r][3] = u.z; pt[r][4] = u.w;
-        pt[r][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xr, ol[r], 0, 0));
-        pt[r][5] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xr, orr[r], 0, 0));
+        const auto u = __builtin_amdgcn_raw_buffer_load_b128(xr, om[r], 0, 0);
+        p.v[r][0] = u[0]; p.v[r][1] = u[1]; p.v[r][2] = u[2]; p.v[r][3] = u[3];
+        p.e[r] = __builtin_amdgcn_raw_buffer_load_b32(xr, oe[r], 0, 0);
       }
     }
   };
+  // the lane's 4 x 6 inputs.  The columns beside its four are its neighbours'
+  // (16 lanes across, a DPP row each); the outer lanes keep the one they loaded.
+  auto patch = [&](const Rows& p, float (&pt)[4][6]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        pt[r][1 + q] = __uint_as_float(!BF ? p.v[r][q & (NW - 1)]
+                                           : q & 1 ? p.v[r][q >> 1] & 0xFFFF0000u : p.v[r][q >> 1] << 16);
+      const int e = static_cast<int>(BF ? p.e[r] << 16 : p.e[r]);
+      pt[r][0] = __int_as_float(__builtin_amdgcn_update_dpp(e, __float_as_int(pt[r][4]), 0x111, 0xF, 0xF, false));
+      pt[r][5] = __int_as_float(__builtin_amdgcn_update_dpp(e, __float_as_int(pt[r][1]), 0x101, 0xF, 0xF, false));
+    }
+  };
 
-  float acc[NF][2][4];
+  float acc[NF][2][4], acc1[NF][2][4];   // sums over the even and the odd channels
 #pragma unroll
   for (int s = 0; s < NF; ++s)
 #pragma unroll
     for (int r = 0; r < 2; ++r)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc[s][r][q] = 0.0f;
+      for (int q = 0; q < 4; ++q) acc[s][r][q] = acc1[s][r][q] = 0.0f;
 
-  // one channel: FMAs over pt while the next channel's rows load into nx
-  // (unconditionally: the last step reloads its own channel, so the loads
-  // are not in a branch the compiler would place after the FMAs)
-  auto step = [&](int c, float (&pt)[4][6], float (&nx)[4][6]) __attribute__((always_inline)) {
-    load_patch(c + 1 < a.c_in ? c + 1 : c, nx);
+  // one channel: its FMAs, then its registers take the rows of the channel
+  // kFewAhead further on (unconditionally: past the last channel that one's
+  // again, so the loads are not in a branch the compiler would place after
+  // the FMAs)
+  auto step = [&](int c, Rows& p, float (&acc)[NF][2][4]) __attribute__((always_inline)) {
+    float pt[4][6];
+    patch(p, pt);
     const float* wc = wtab + c * WPC;
 #pragma unroll
     for (int s = 0; s < NF; ++s)
@@ -169,14 +193,26 @@ __global__ __launch_bounds__(256) void pp_conv3x3_fewout_kernel(ConvParams a) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) acc[s][r][q] = __builtin_fmaf(wv, pt[r + ky][q + kx], acc[s][r][q]);
         }
+    load_rows(min(c + kFewAhead, a.c_in - 1), p);
+    __builtin_amdgcn_sched_barrier(0);
   };
-  float pa[4][6], pb[4][6];
-  load_patch(0, pa);
+  Rows rows[kFewAhead];
+#pragma unroll
+  for (int i = 0; i < kFewAhead; ++i) load_rows(min(i, a.c_in - 1), rows[i]);
 #pragma unroll 1
-  for (int c = 0; c < a.c_in; c += 2) {
-    step(c, pa, pb);
-    if (c + 1 < a.c_in) step(c + 1, pb, pa);
-  }
+  for (int c = 0; c + kFewAhead <= a.c_in; c += kFewAhead)
+#pragma unroll
+    for (int i = 0; i < kFewAhead; ++i) step(c + i, rows[i], i & 1 ? acc1 : acc);
+  const int rest = a.c_in % kFewAhead;
+#pragma unroll
+  for (int i = 0; i < kFewAhead - 1; ++i)
+    if (i < rest) step(a.c_in - rest + i, rows[i], i & 1 ? acc1 : acc);
+#pragma unroll
+  for (int s = 0; s < NF; ++s)
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[s][r][q] += acc1[s][r][q];
 
   // ---- epilogue: + bias, ReLU, store through perm (slot s of group 0)
   if (!lane_in) return;

@@ -53,3 +53,12 @@ def test_workspace_covers_the_matrix_core_form():
     b = _blob(12, 64, 64, pp.PP_BF16)
     ws = pp.conv2d_workspace(b, 1, 270, 480, pp.PP_BF16)
     assert ws >= 64 * 9 * 64 * 2 + 64 * 4   # the expanded weights and the bias
+
+
+def test_large_fp32_image_layers_take_the_few_output_kernel():
+    full = _blob(13, 3, 64, pp.PP_F32, keep=1.0, lib=workloads.DENSE9)
+    assert pp.conv2d_recipe(full, 1, 1080, 1920, pp.PP_F32) == 61
+    assert pp.conv2d_recipe(full, 1, 540, 960, pp.PP_F32) != 61     # small: the wave kernel
+    assert pp.conv2d_recipe(full, 2, 1080, 1920, pp.PP_F32) != 61   # a batch
+    some = _blob(14, 3, 64, pp.PP_F32, keep=0.9, lib=workloads.DENSE9)
+    assert pp.conv2d_recipe(some, 1, 1080, 1920, pp.PP_F32) != 61   # a pruned kernel
