@@ -275,7 +275,8 @@ def _dtype_code(t) -> int:
 
 def _stream_ptr(stream=None) -> int:
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
+    # (with the device given, torch skips a lookup of 1.4 us)
+    s = stream if stream is not None else torch.cuda.current_stream(torch.cuda.current_device())
     return int(s.cuda_stream)
 
 
@@ -289,6 +290,8 @@ class PackedLayer:
         self.d_blob = torch.from_numpy(self.h_blob.copy()).to(device)
         if self.d_blob.data_ptr() % 256:
             raise RuntimeError("device blob allocation is not 256-byte aligned")
+        # the host blob's address and size (numpy's .ctypes view costs microseconds a call)
+        self._h_ptr, self._h_bytes = self.h_blob.ctypes.data, self.h_blob.nbytes
         self.scratch = {}   # conv2d_fwd workspaces by input shape
         self.prepared = None   # matrix-core weights (prepare())
 
@@ -313,6 +316,23 @@ class PackedLayer:
                                      ctypes.byref(nb), _stream_ptr(stream)), "pp_conv2d_prepare")
         self.prepared = buf
         return buf
+
+    def _out_size(self, h, w):
+        """out_size of this layer, from its description alone."""
+        i = self.info
+        hn = h + 2 * i["pad"] - 2 * i["dilation"] - 1
+        wn = w + 2 * i["pad"] - 2 * i["dilation"] - 1
+        if h < 1 or w < 1 or hn < 0 or wn < 0:
+            return out_size(self.h_blob, h, w)   # raises the library's error
+        return hn // i["stride"] + 1, wn // i["stride"] + 1
+
+    def _workspace(self, n, h, w, act_dtype) -> int:
+        """conv2d_workspace of this layer (asked every call: forced plans and
+        run-time compiled kernels change it)."""
+        b = ctypes.c_size_t(0)
+        _check(load_library().pp_conv2d_workspace(self._h_ptr, self._h_bytes, n, h, w, act_dtype, ctypes.byref(b)),
+               "pp_conv2d_workspace")
+        return b.value
 
     @classmethod
     def from_weights(cls, w, b, pattern_id, conn, lib_masks, stride=1, pad=1, dilation=1, wdtype=PP_F32,
@@ -343,7 +363,8 @@ def conv2d_fwd(layer: PackedLayer, x, relu=False, out=None, stream=None, workspa
     if c != layer.info["c_in"]:
         raise ValueError(f"x has {c} channels, the layer expects {layer.info['c_in']}")
     hc, wc = (2 * h, 2 * w) if upsample2 else (h, w)   # the conv's input size
-    ho, wo = out_size(layer.h_blob, hc, wc)
+    ho, wo = layer._out_size(hc, wc)
+    dt = _dtype_code(x)
     c_out = layer.info["c_out"]
     if maxpool2:
         ho, wo = ho // 2, wo // 2
@@ -353,23 +374,23 @@ def conv2d_fwd(layer: PackedLayer, x, relu=False, out=None, stream=None, workspa
     if accumulate and out is None:
         raise ValueError("accumulate needs out (the residual, updated in place)")
     if out is None:
-        out = torch.empty(shape, dtype=x.dtype, device=x.device)
+        out = x.new_empty(shape)
     elif tuple(out.shape) != shape or out.dtype != x.dtype or not out.is_contiguous():
         raise ValueError(f"out must be a contiguous {x.dtype} tensor of shape {shape}")
     if prepared:
-        nb = conv2d_workspace(layer.h_blob, n, hc, wc, _dtype_code(x))
+        nb = layer._workspace(n, hc, wc, dt)
         workspace = layer.prepared
         if nb:
-            key = ("prepared", n, hc, wc, _dtype_code(x), x.device.index)
+            key = ("prepared", n, hc, wc, dt, x.device.index)
             head = -(-layer.prepared.numel() // 256) * 256
             workspace = layer.scratch.get(key)
-            if workspace is None:
+            if workspace is None or workspace.numel() < head + nb:
                 workspace = torch.empty(head + nb, dtype=torch.uint8, device=x.device)
                 workspace[:layer.prepared.numel()].copy_(layer.prepared)
                 layer.scratch[key] = workspace
     elif isinstance(workspace, str) and workspace == "auto":
-        nb = conv2d_workspace(layer.h_blob, n, hc, wc, _dtype_code(x))
-        key = (n, hc, wc, _dtype_code(x), x.device.index)
+        nb = layer._workspace(n, hc, wc, dt)
+        key = (n, hc, wc, dt, x.device.index)
         workspace = layer.scratch.get(key)
         if nb and (workspace is None or workspace.numel() < nb):
             workspace = torch.empty(nb, dtype=torch.uint8, device=x.device)
@@ -377,8 +398,8 @@ def conv2d_fwd(layer: PackedLayer, x, relu=False, out=None, stream=None, workspa
         if not nb:
             workspace = None
     ws_ptr, ws_bytes = (workspace.data_ptr(), workspace.numel()) if workspace is not None else (None, 0)
-    st = lib.pp_conv2d_fwd(_ptr(layer.h_blob), layer.h_blob.nbytes, layer.d_blob.data_ptr(), x.data_ptr(),
-                           out.data_ptr(), n, h, w, _dtype_code(x),
+    st = lib.pp_conv2d_fwd(layer._h_ptr, layer._h_bytes, layer.d_blob.data_ptr(), x.data_ptr(),
+                           out.data_ptr(), n, h, w, dt,
                            (PP_RELU if relu else 0) | (PP_MAXPOOL2 if maxpool2 else 0) |
                            (PP_ACCUMULATE if accumulate else 0) | (PP_PIXSHUF2 if pixshuf2 else 0) |
                            (PP_UPSAMPLE2 if upsample2 else 0) | (PP_PREPARED if prepared else 0), ws_ptr, ws_bytes,
