@@ -290,8 +290,6 @@ class PackedLayer:
         self.d_blob = torch.from_numpy(self.h_blob.copy()).to(device)
         if self.d_blob.data_ptr() % 256:
             raise RuntimeError("device blob allocation is not 256-byte aligned")
-        # the host blob's address and size (numpy's .ctypes view costs microseconds a call)
-        self._h_ptr, self._h_bytes = self.h_blob.ctypes.data, self.h_blob.nbytes
         self.scratch = {}   # conv2d_fwd workspaces by input shape
         self.prepared = None   # matrix-core weights (prepare())
 
@@ -317,6 +315,24 @@ class PackedLayer:
         self.prepared = buf
         return buf
 
+    # The host blob, with its address beside it for the calls (numpy's .ctypes
+    # view takes 1.2 us); a copied or unpickled layer has a blob of its own.
+    @property
+    def h_blob(self) -> np.ndarray:
+        return self._h_blob
+
+    @h_blob.setter
+    def h_blob(self, blob):
+        self._h_blob, self._h_ptr = blob, blob.ctypes.data
+
+    def __getstate__(self):
+        d = {k: v for k, v in self.__dict__.items() if k not in ("_h_blob", "_h_ptr")}
+        return {"h_blob": self._h_blob, **d}
+
+    def __setstate__(self, state):
+        for k, v in state.items():
+            setattr(self, k, v)
+
     def _out_size(self, h, w):
         """out_size of this layer, from its description alone."""
         i = self.info
@@ -330,7 +346,7 @@ class PackedLayer:
         """conv2d_workspace of this layer (asked every call: forced plans and
         run-time compiled kernels change it)."""
         b = ctypes.c_size_t(0)
-        _check(load_library().pp_conv2d_workspace(self._h_ptr, self._h_bytes, n, h, w, act_dtype, ctypes.byref(b)),
+        _check(load_library().pp_conv2d_workspace(self._h_ptr, self._h_blob.nbytes, n, h, w, act_dtype, ctypes.byref(b)),
                "pp_conv2d_workspace")
         return b.value
 
@@ -398,7 +414,7 @@ def conv2d_fwd(layer: PackedLayer, x, relu=False, out=None, stream=None, workspa
         if not nb:
             workspace = None
     ws_ptr, ws_bytes = (workspace.data_ptr(), workspace.numel()) if workspace is not None else (None, 0)
-    st = lib.pp_conv2d_fwd(layer._h_ptr, layer._h_bytes, layer.d_blob.data_ptr(), x.data_ptr(),
+    st = lib.pp_conv2d_fwd(layer._h_ptr, layer._h_blob.nbytes, layer.d_blob.data_ptr(), x.data_ptr(),
                            out.data_ptr(), n, h, w, dt,
                            (PP_RELU if relu else 0) | (PP_MAXPOOL2 if maxpool2 else 0) |
                            (PP_ACCUMULATE if accumulate else 0) | (PP_PIXSHUF2 if pixshuf2 else 0) |

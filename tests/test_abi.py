@@ -132,6 +132,25 @@ def test_conv_validation_happens_before_any_launch(lib):
     assert _conv(lib, _blob(pad=0, dil=2), h=4, w=4) == pp.PP_EUNSUPPORTED   # smaller than the dilated kernel
 
 
+@pytest.mark.parametrize("how", ["deepcopy", "pickle", "rebound"])
+def test_copied_layer_calls_with_its_own_blob(lib, how):
+    import copy
+    import pickle
+    op = workloads.net_spec(1)["ops"][0]
+    L = workloads.layer_params(1, 0, op)
+    blob = pp.pack(L["w"], L["b"], L["pid"], L["conn"], L["lib"])
+    layer = pp.PackedLayer.__new__(pp.PackedLayer)   # (no device copy)
+    layer.h_blob, layer.info = blob, pp.blob_info(blob)
+    if how == "rebound":
+        other = layer
+        other.h_blob = blob.copy()
+    else:
+        other = copy.deepcopy(layer) if how == "deepcopy" else pickle.loads(pickle.dumps(layer))
+    assert other.h_blob is not blob and np.array_equal(other.h_blob, blob)
+    assert other._h_ptr == other.h_blob.ctypes.data != blob.ctypes.data
+    assert other._workspace(1, 14, 14, pp.PP_F32) == pp.conv2d_workspace(blob, 1, 14, 14, pp.PP_F32)
+
+
 def test_out_size(lib):
     for (s, p, d, h, w) in ((1, 1, 1, 32, 32), (2, 1, 1, 33, 20), (1, 2, 2, 10, 7), (2, 0, 1, 9, 9)):
         ho, wo = pp.out_size(_blob(stride=s, pad=p, dil=d), h, w)
