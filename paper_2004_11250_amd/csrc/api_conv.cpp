@@ -184,7 +184,15 @@ bool conv_fusable(const BlobView& v, int32_t n, int32_t h, int32_t w, int32_t ac
   p.flags = flags;
   const int lib = library_kind(v);
   const bool bf = act_dtype == PP_BF16;
-  if (plan_conv(p, lib, bf, with_scratch).recipe < 0) return false;
+  const ConvPlan fused = plan_conv(p, lib, bf, with_scratch);
+  if (fused.recipe < 0) return false;
+  // an upsample or a pixel shuffle that would take a conv off the matrix cores
+  // stays unfused, for the reason below
+  if (bf && fused.recipe != kRecipeMfma && (flags & (PP_UPSAMPLE2 | PP_PIXSHUF2))) {
+    ConvParams q = p;
+    q.flags = flags & ~static_cast<uint32_t>(PP_UPSAMPLE2 | PP_PIXSHUF2);
+    if (plan_conv(q, lib, bf, with_scratch).recipe == kRecipeMfma) return false;
+  }
   // a bf16 conv that runs on the lean kernel unfused is not fused with an
   // upsample or a pixel shuffle, which that kernel does not take: the fused
   // conv would run on another kernel, whose sums round differently

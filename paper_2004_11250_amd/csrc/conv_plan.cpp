@@ -172,40 +172,49 @@ static bool pool_fits(int id) {
 }
 
 // whether the matrix-core form of a bf16 layer beats the vector kernels: a
-// time model of each, its constants fitted to the bf16 layers of the five
-// workloads on MI355X.  The wave-pipeline kernel does n_wt MACs per output
-// pixel (n_wt: stored weights, about the surviving taps) at about 12 T MAC/s
-// (half that at stride 2); the lean kernel (lean: it can run the layer) costs
-// about one step per (output pixel, input channel, slot group), pruned slots
-// all but free, plus 5 us, at a rate set by the tiling the lean table picks:
-// about 1.0 T steps/s for the 4 x 4 tilings (maps from 160 x 160 up to
-// 256 x 256 and from 512 x 512, or batches of 64 K outputs and more), 1.25 T
-// for 2 x 4 on maps in between, 1.5 T on maps from 80 x 80, 1.1 T below (with prepared weights: VGG-16's layers 14-28 us, the style
-// network's 128 -> 128 at 128 x 128 25.6 us).  The matrix-core form is
-// latency-bound while the chip
-// holds all its workgroups (about 1.4-1.5 us per k step, each waiting for
-// its own loads), else bound by workgroup steps (about 880 / 390 per us for
-// 64 / 128-filter tiles); plus about 8 us for the weight expansion and its
-// launch.
+// time model of each, fitted on MI355X over the VGG-16, super-resolution and
+// colourization layer shapes and others of their range (30 shapes, kept shares
+// of 0.25 and 0.6).  The wave-pipeline kernel does n_wt MACs per output pixel
+// (n_wt: stored weights, about the surviving taps) at about 12 T MAC/s (half
+// that at stride 2), and its small grids wait for each channel (0.07 us, 0.19
+// at stride 2: 512 -> 512 at 32 x 32 108 us, 41 here; 0.02 on single maps
+// below 20 x 20, whose channels it splits).  The lean kernel (lean:
+// it can run the layer) costs about one step per (output pixel, input channel,
+// slot group), 5 us beside them, at a rate set by the tiling the lean table
+// picks: for a third of the kernels kept about 1.0 T steps/s for the 4 x 4
+// tilings (maps from 160 x 160 up to 256 x 256 and from 512 x 512, or batches
+// of 64 K outputs and more), 1.25 T for 2 x 4 on maps in between, 1.5 T on
+// maps from 80 x 80, 1.1 T below; more for fewer kernels, less for more
+// (256 -> 256 at 56 x 56 22 us at a quarter kept, 29.5 at 0.6; 17 here).
+// Batches run whole 16 x 32 tiles of each map.  With weights prepared or
+// not, the form has to win: the expansion on each call takes 3 us and 7 more
+// at 512 -> 512, the vector kernels' unprepared weights about an eighth.
 static bool mfma_pays(const ConvParams& p, bool lean) {
-  const double pix = static_cast<double>(p.n) * p.ho * p.wo;
   const double map = static_cast<double>(p.ho) * p.wo;
-  const double lean_rate = p.n == 1 && map >= 256.0 * 256.0 && map < 512.0 * 512.0 ? 1.25e12
-                           : (p.n > 1 ? pix >= 65536.0 : map >= 160.0 * 160.0) ? 1.0e12
-                           : (p.n > 1 || map >= 80.0 * 80.0)                 ? 1.5e12
-                                                                              : 1.1e12;
-  const double t_vec = lean ? pix * p.c_in * p.n_groups / lean_rate + 5e-6
-                            : pix * p.n_wt * (p.stride == 2 ? 2.2 : 1.0) / 12e12 + 8e-6;
-  const bool long_k = 9 * p.c_in >= 1152;
-  const int km = long_k ? 64 : 32;
-  const double steps = (9.0 * p.c_in + km - 1) / km;
-  const long bm = p.c_out > 64 ? 128 : 64;
-  const double wgs = std::ceil(pix / 128) * ((p.c_out + bm - 1) / bm);
-  // (two wave groups per tile when the grid is at most one tile per compute
-  // unit: about 0.8 of the latency-bound time)
-  const double lat = steps * (long_k ? 1.5e-6 : 1.4e-6) * (wgs <= 256 ? 0.8 : 1.0);
-  const double t_mfma = std::max(lat, wgs * steps / (bm == 128 ? 390e6 : 880e6)) + 8e-6;
-  return t_mfma < t_vec;
+  const double pix = p.n * map;
+  double t_vec;
+  if (lean) {
+    const double run = p.n > 1 ? static_cast<double>(p.n) * ((p.ho + 15) / 16 * 16) * ((p.wo + 31) / 32 * 32) : pix;
+    const double rate = p.n == 1 && map >= 256.0 * 256.0 && map < 512.0 * 512.0 ? 1.25e12
+                        : (p.n > 1 ? pix >= 65536.0 : map >= 160.0 * 160.0) ? 1.0e12
+                        : (p.n > 1 || map >= 80.0 * 80.0)                 ? 1.5e12
+                                                                          : 1.1e12;
+    const double kept = p.n_wt / (4.0 * p.c_in * p.c_out);
+    const double t_steps = run * p.c_in * p.n_groups / rate;
+    // one image of 80 x 80 to 160 x 160 outputs over 128 channels or more, up
+    // to 24 us, keeps the lean kernel: a choice that callers rely on, though
+    // this form is faster now (128 -> 128 at 128 x 128 with prepared weights
+    // 12 us against 24, with the expansion 16 against 27)
+    if (p.n == 1 && p.c_in >= 128 && map >= 80.0 * 80.0 && map < 160.0 * 160.0 && t_steps < 24e-6) return false;
+    t_vec = t_steps * (0.63 + 1.1 * std::min(kept, 1.0)) + 5e-6;
+  } else {
+    const bool s2 = p.stride == 2;
+    const double wait = s2 ? 0.19e-6 : p.n == 1 && map < 20.0 * 20.0 ? 0.02e-6 : 0.07e-6;   // (the smallest run split)
+    t_vec = std::max(pix * p.n_wt * (s2 ? 2.2 : 1.0) / 12e12, p.c_in * wait) + 8e-6;
+  }
+  const double t_mfma = mfma_time(p);
+  const double expand = 3e-6 + 7e-6 * p.c_in * p.c_out / (512.0 * 512.0);
+  return t_mfma < t_vec && t_mfma + expand < 1.12 * t_vec;
 }
 
 ConvPlan plan_conv(const ConvParams& p, int lib, bool bf16, bool allow_split, bool no_lean) {

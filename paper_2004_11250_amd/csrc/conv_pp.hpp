@@ -206,6 +206,7 @@ constexpr int kRecipeFewOut = 61;
 bool fewout_eligible(const ConvParams& p);
 hipError_t launch_fewout_conv(const ConvParams& p, bool bf16_act, hipStream_t st);
 bool mfma_eligible(const ConvParams& p);
+double mfma_time(const ConvParams& p);   // modelled seconds of its launch, weights expanded
 size_t mfma_bytes(const ConvParams& p);
 hipError_t launch_mfma_conv(const ConvParams& p, hipStream_t st);   // PP_PREPARED in p.flags: no expansion
 hipError_t launch_mfma_expand(const ConvParams& p, void* out, hipStream_t st);   // the weights into out

@@ -22,6 +22,7 @@
 // as the vector kernels do.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "conv_pp_kernel.hpp"
@@ -86,6 +87,7 @@ __global__ __launch_bounds__(256) void pp_mfma_expand_kernel(ConvParams a, uint1
     uint16_t v = 0;
     if ((m >> t) & 1u) {
       v = idx < a.n_wt ? w[idx] : static_cast<uint16_t>(0);
+      if (v == 0) v = 0x8000u;   // a stored zero: +0 is left for taps that are not there
       ++idx;
     }
     dst[static_cast<size_t>(t) * 16 * rows] = v;
@@ -298,6 +300,52 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
     lds_barrier();
   }
 
+  // A pruned tap's zero weight times an infinity of the input is NaN, where the
+  // vector kernels never read that tap: outputs that came out NaN are summed
+  // again over the taps that are there.  Found by one FMA per accumulator pair
+  // (NaN stays; a false alarm only costs the look), 0.5 % of a 128 x 256 tile.
+  float probe = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) probe = __builtin_fmaf(acc[i][j][r], acc[i][j][r + 1], probe);
+  if (__any(probe != probe)) {
+    const uint16_t* xi = static_cast<const uint16_t*>(a.x) + static_cast<size_t>(img) * a.c_in * hw;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int oy = oy0 + prow + j * M::RPB, ox = ox0 + pcol;
+        uint32_t bad = 0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) bad |= acc[i][j][r] != acc[i][j][r] ? 1u << r : 0u;
+        if (oy >= a.ho || ox >= a.wo) bad = 0;
+#pragma unroll 1
+        while (bad) {
+          const int r = __builtin_ctz(bad);
+          bad &= bad - 1;
+          const int o = mtile * M::BM + (wm * 2 + i) * 32 + 8 * (r >> 2) + (lane >> 5) * 4 + (r & 3);
+          if (o >= a.c_out) continue;
+          const int rows = min(32, a.c_out - (o & ~31));
+          const uint16_t* wp = am + static_cast<size_t>(o >> 5) * 32 * 9 * a.c_in + (o & 31) * 8;
+          float sum = 0.0f;
+#pragma unroll 1
+          for (int e = 0; e < 9 * a.c_in && sum == sum; ++e) {
+            const int c = e / 9, t = e % 9;
+            const uint32_t wt = wp[static_cast<size_t>((c >> 4) * 18 + t * 2 + ((c >> 3) & 1)) * rows * 8 + (c & 7)];
+            const int gy = oy * S - a.pad + t / 3 * D, gx = ox * S - a.pad + t % 3 * D;
+            if (wt == 0 || gy < 0 || gy >= a.h || gx < 0 || gx >= a.w) continue;
+            const size_t el = up ? static_cast<size_t>(gy >> 1) * wsd + (gx >> 1) : static_cast<size_t>(gy) * wsd + gx;
+            sum = __builtin_fmaf(bf16_val(wt), bf16_val(xi[static_cast<size_t>(c) * hw + el]), sum);
+          }
+#pragma unroll
+          for (int k = 0; k < 16; ++k) acc[i][j][k] = k == r ? sum : acc[i][j][k];
+        }
+      }
+  }
+
   // accumulator r of block (i, j), lane l, is C[8 (r / 4) + 4 (l / 32) + r % 4][l % 32] of the block.
   // A row's address is a wave-uniform base (filter 8 (r / 4) + r % 4) plus a
   // 32-bit lane offset (4 filters for the upper half of the wave, and the pixel).
@@ -405,6 +453,30 @@ long tiles(const ConvParams& p, int bm, int th, int tw) {
   return static_cast<long>((p.c_out + bm - 1) / bm) * ((p.ho + th - 1) / th) * ((p.wo + tw - 1) / tw) * p.n;
 }
 
+// Tiles (filters x pixels; timed on MI355X, bf16, us): the weights cross
+// each compute unit's caches once per wave, so larger tiles are better as
+// long as every unit still gets one or two workgroups.
+//   128 x 256 from 512 such tiles (64 -> 256 at 270 x 480: 44, 128 x 128 47;
+//     512 -> 512 on 8 x 32 x 32, 128 tiles: 60 against 37)
+//   128 x 128 from 192 (that layer; 128 -> 256 on 8 x 64 x 64: 23, 64 x 128 33)
+//   64 x 256 for at most 64 filters from 400 (64 -> 64 at 270 x 480: 18, 64 x 128 21)
+//   64 x 128 below (128 -> 128 at 128 x 128: 12.3, 128 x 128 14)
+// 128 x 128 stages 64 channels at a time when c_in is a multiple of 64 (one workgroup per
+// unit: half the waits for a block's input; 512 -> 512: 37 against 39).  The
+// 128-pixel tiles are 4 x 32 or 8 x 16 outputs, whichever covers the map with fewer tiles.
+// Every tile sums in the same order: the choice never changes a result's bits.
+enum Form { kS2, kS2Wide, k128x256, k64x256, k128x128, k64x128 };
+
+bool is_tall(const ConvParams& p) { return tiles(p, 128, 8, 16) < tiles(p, 128, 4, 32); }   // 8 x 16 covers the map with fewer
+
+Form choose_form(const ConvParams& p) {
+  const bool wide = p.c_out > 64, d1 = p.dil == 1;
+  if (p.stride == 2) return d1 && wide && tiles(p, 128, 4, 32) >= 192 ? kS2Wide : kS2;
+  if (d1 && wide && tiles(p, 128, 8, 32) >= 512) return k128x256;
+  if (d1 && !wide && tiles(p, 64, 8, 32) >= 400) return k64x256;
+  return wide && std::min(tiles(p, 128, 8, 16), tiles(p, 128, 4, 32)) >= 192 ? k128x128 : k64x128;
+}
+
 template <int WM, int TN, int CB, int TW, int S, int D>
 hipError_t launch_tiles(const ConvParams& p, const uint16_t* am, const float* bo, hipStream_t st) {
   using M = MGeo<WM, TN, CB, TW, S, D>;
@@ -440,6 +512,28 @@ bool mfma_eligible(const ConvParams& p) {
          static_cast<size_t>(p.c_out) * 9 * p.c_in * 2 < (size_t{1} << 30);
 }
 
+// A workgroup's time is linear in c_in (what bounds it is the weights' way
+// through its unit's cache, the same for every channel), and workgroups past
+// one per unit queue.  us per input channel, measured on MI355X: 64 x 128
+// 0.0455 (512 -> 512 at 14 x 14 28.1, 256 -> 256 at 20 x 30 16.8, 64 -> 64 at
+// 224 x 224, 392 tiles, 12.1), 128 x 128 0.0625 (512 -> 512 on 8 x 32 x 32
+// 37), 64 x 256 0.105, 128 x 256 0.16 (64 -> 256 at 540 x 960 170), stride 2
+// 0.072 (512 -> 512 at 32 x 32 41.5), its 128 x 128 0.1; 5 us to launch, fill
+// and drain.
+double mfma_time(const ConvParams& p) {
+  double us = 0.0455;
+  long t = std::min(tiles(p, 64, 8, 16), tiles(p, 64, 4, 32));
+  switch (choose_form(p)) {
+    case kS2: us = 0.072, t = tiles(p, 64, 4, 32); break;
+    case kS2Wide: us = 0.1, t = tiles(p, 128, 4, 32); break;
+    case k128x256: us = 0.16, t = tiles(p, 128, 8, 32); break;
+    case k64x256: us = 0.105, t = tiles(p, 64, 8, 32); break;
+    case k128x128: us = 0.0625, t = std::min(tiles(p, 128, 8, 16), tiles(p, 128, 4, 32)); break;
+    case k64x128: break;
+  }
+  return (5.0 + us * p.c_in * std::max(1.0, t / 256.0)) * 1e-6;
+}
+
 size_t mfma_bytes(const ConvParams& p) { return a_bytes(p) + static_cast<size_t>(p.c_out) * sizeof(float); }
 
 hipError_t launch_mfma_expand(const ConvParams& p, void* out, hipStream_t st) {
@@ -460,36 +554,22 @@ hipError_t launch_mfma_conv(const ConvParams& p, hipStream_t st) {
     const hipError_t e = launch_mfma_expand(p, p.part, st);
     if (e != hipSuccess) return e;
   }
-  // Tiles (filters x pixels; timed on MI355X, bf16, us): the weights cross
-  // each compute unit's caches once per wave, so larger tiles are better as
-  // long as every unit still gets one or two workgroups.
-  //   128 x 256 from 512 such tiles (64 -> 256 at 270 x 480: 44, 128 x 128 47;
-  //     512 -> 512 on 8 x 32 x 32, 128 tiles: 60 against 37)
-  //   128 x 128 from 192 (that layer; 128 -> 256 on 8 x 64 x 64: 23, 64 x 128 33)
-  //   64 x 256 for at most 64 filters from 400 (64 -> 64 at 270 x 480: 18, 64 x 128 21)
-  //   64 x 128 below (128 -> 128 at 128 x 128: 12.3, 128 x 128 14)
-  // 128 x 128 stages 64 channels at a time when c_in is a multiple of 64 (one workgroup per
-  // unit: half the waits for a block's input; 512 -> 512: 37 against 39).  The
-  // 128-pixel tiles are 4 x 32 or 8 x 16 outputs, whichever covers the map with fewer tiles.
-  // Every tile sums in the same order: the choice never changes a result's bits.
-  const bool wide = p.c_out > 64, d1 = p.dil == 1;
-  if (p.stride == 2) {
-    if (!d1) return launch_tiles<1, 1, 16, 32, 2, 2>(p, am, bo, st);
-    if (wide && tiles(p, 128, 4, 32) >= 192) return launch_tiles<2, 2, 32, 32, 2, 1>(p, am, bo, st);
-    return launch_tiles<1, 1, 16, 32, 2, 1>(p, am, bo, st);
+  const bool d1 = p.dil == 1;
+  switch (choose_form(p)) {
+    case kS2: return d1 ? launch_tiles<1, 1, 16, 32, 2, 1>(p, am, bo, st) : launch_tiles<1, 1, 16, 32, 2, 2>(p, am, bo, st);
+    case kS2Wide: return launch_tiles<2, 2, 32, 32, 2, 1>(p, am, bo, st);
+    case k128x256: return launch_tiles<2, 4, 32, 32, 1, 1>(p, am, bo, st);
+    case k64x256: return launch_tiles<1, 2, 32, 32, 1, 1>(p, am, bo, st);
+    case k128x128:
+      if (p.c_in % 64 == 0) {
+        if (is_tall(p)) return d1 ? launch_tiles<2, 2, 64, 16, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 64, 16, 1, 2>(p, am, bo, st);
+        return d1 ? launch_tiles<2, 2, 64, 32, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 64, 32, 1, 2>(p, am, bo, st);
+      }
+      if (is_tall(p)) return d1 ? launch_tiles<2, 2, 32, 16, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 32, 16, 1, 2>(p, am, bo, st);
+      return d1 ? launch_tiles<2, 2, 32, 32, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 32, 32, 1, 2>(p, am, bo, st);
+    case k64x128: break;
   }
-  if (d1 && wide && tiles(p, 128, 8, 32) >= 512) return launch_tiles<2, 4, 32, 32, 1, 1>(p, am, bo, st);
-  if (d1 && !wide && tiles(p, 64, 8, 32) >= 400) return launch_tiles<1, 2, 32, 32, 1, 1>(p, am, bo, st);
-  const bool tall = tiles(p, 128, 8, 16) < tiles(p, 128, 4, 32);   // 8 x 16 covers the map with fewer
-  if (wide && tiles(p, 128, tall ? 8 : 4, tall ? 16 : 32) >= 192) {
-    if (p.c_in % 64 == 0) {
-      if (tall) return d1 ? launch_tiles<2, 2, 64, 16, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 64, 16, 1, 2>(p, am, bo, st);
-      return d1 ? launch_tiles<2, 2, 64, 32, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 64, 32, 1, 2>(p, am, bo, st);
-    }
-    if (tall) return d1 ? launch_tiles<2, 2, 32, 16, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 32, 16, 1, 2>(p, am, bo, st);
-    return d1 ? launch_tiles<2, 2, 32, 32, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 32, 32, 1, 2>(p, am, bo, st);
-  }
-  if (tall) return d1 ? launch_tiles<1, 1, 32, 16, 1, 1>(p, am, bo, st) : launch_tiles<1, 1, 32, 16, 1, 2>(p, am, bo, st);
+  if (is_tall(p)) return d1 ? launch_tiles<1, 1, 32, 16, 1, 1>(p, am, bo, st) : launch_tiles<1, 1, 32, 16, 1, 2>(p, am, bo, st);
   return d1 ? launch_tiles<1, 1, 32, 32, 1, 1>(p, am, bo, st) : launch_tiles<1, 1, 32, 32, 1, 2>(p, am, bo, st);
 }
 

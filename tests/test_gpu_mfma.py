@@ -284,3 +284,35 @@ def test_mfma_tiles(case, monkeypatch):
     off.copy_(xd)
     assert off.data_ptr() % 4 == 2
     assert torch.equal(pp.conv2d_fwd(layer, off, relu=True), yd)   # same sums, other loads
+
+
+@pytest.mark.parametrize("case", [
+    ("canon8", (1, 1, 1), (1, 64, 64, 20, 34), 0.5),
+    ("canon8", (1, 1, 1), (2, 40, 32, 13, 21), 0.4),     # odd width, ragged filters
+    ("canon8", (2, 1, 1), (1, 136, 32, 17, 22), 0.5),
+    ("mixed", (1, 2, 2), (1, 72, 64, 16, 18), 0.5),
+    ("canon8", (1, 1, 1), (1, 256, 32, 96, 320), 0.3),   # 128 x 128 tiles
+])
+def test_mfma_infinities_reach_kept_taps_only(case, monkeypatch):
+    # a pruned tap never meets an infinity or NaN of the input, as on the
+    # vector kernels; a stored weight of zero is a kept tap
+    lib, (s, p, d), (n, c_out, c_in, h, w), keep = case
+    L = workloads.random_layer(1400, c_out, c_in, lib=LIBS[lib], keep=keep)
+    L["w"][0, :, 1, 1] = 0.0
+    layer = pp.PackedLayer.from_weights(L["w"], L["b"], L["pid"], L["conn"], L["lib"], s, p, d, pp.PP_BF16)
+    x = _dev(workloads.random_input(1400, (n, c_in, h, w)))
+    x[0, 3, 5, 7], x[0, 17, 0, 0], x[-1, 9, h - 1, w - 1] = float("inf"), float("-inf"), float("nan")
+    x[0, 21, 5, 8] = float("inf")
+    _say("mfma infinities", case)
+    monkeypatch.setenv("PP_RECIPE", "64")
+    assert pp.conv2d_recipe(layer.h_blob, n, h, w, pp.PP_BF16) == MFMA
+    y = pp.conv2d_fwd(layer, x)
+    monkeypatch.setenv("PP_RECIPE", "13")
+    assert pp.conv2d_recipe(layer.h_blob, n, h, w, pp.PP_BF16) == 13
+    ref = pp.conv2d_fwd(layer, x, workspace=None)
+    y, ref = y.float(), ref.float()
+    fin = torch.isfinite(ref)
+    assert 0 < int((~fin).sum()) < fin.numel() // 4
+    assert torch.equal(y[~fin].nan_to_num(nan=7.0), ref[~fin].nan_to_num(nan=7.0))
+    # (both round an fp32 sum once: a bf16 ulp apart at most)
+    assert torch.all((y[fin] - ref[fin]).abs() <= 2 ** -7 * ref[fin].abs() + 1e-5)

@@ -62,3 +62,20 @@ def test_large_fp32_image_layers_take_the_few_output_kernel():
     assert pp.conv2d_recipe(full, 2, 1080, 1920, pp.PP_F32) != 61   # a batch
     some = _blob(14, 3, 64, pp.PP_F32, keep=0.9, lib=workloads.DENSE9)
     assert pp.conv2d_recipe(some, 1, 1080, 1920, pp.PP_F32) != 61   # a pruned kernel
+
+
+@pytest.mark.parametrize("c_out,c_in,s,d,n,h,w,keep,mfma", [
+    (64, 64, 1, 1, 1, 224, 224, 1 / 3, True),      # VGG-16, one image (12 us, lean 26)
+    (512, 512, 2, 1, 1, 32, 32, 0.4, True),        # stride 2 (42 us, wave 108)
+    (256, 256, 2, 1, 8, 32, 32, 0.3, True),
+    (64, 128, 1, 2, 2, 40, 40, 0.4, True),         # dilation 2 (10 us, wave 32)
+    (96, 64, 1, 1, 1, 119, 191, 0.3, True),        # odd width
+    (512, 512, 1, 1, 1, 4, 15, 1 / 3, False),      # the smallest maps: split over the channels there
+    (512, 512, 1, 1, 1, 10, 12, 0.6, False),
+    (32, 32, 1, 1, 1, 32, 32, 0.5, False),
+])
+def test_matrix_core_choice_over_the_range(c_out, c_in, s, d, n, h, w, keep, mfma):
+    b = _blob(15, c_out, c_in, pp.PP_BF16, keep=keep, s=s, p=d, d=d)
+    assert (pp.conv2d_recipe(b, n, h, w, pp.PP_BF16) == MFMA) is mfma
+    # without scratch for the expansion: another plan, never a refusal
+    assert pp.conv2d_recipe(b, n, h, w, pp.PP_BF16, with_workspace=False) not in (MFMA, -1)
