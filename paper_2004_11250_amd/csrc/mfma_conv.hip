@@ -104,14 +104,14 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // Tile geometry.  A workgroup is 4 waves, WM along the filters and 4 / WM
-// along the pixels; a wave owns 64 filters (2 blocks of 32) by TN blocks of
-// 32 pixels.  The pixel tile is TH x TW outputs of one image; its input halo
+// along the pixels; a wave owns MB blocks of 32 filters by TN blocks of 32
+// pixels.  The pixel tile is TH x TW outputs of one image; its input halo
 // (HR x HC) is staged CB channels at a time as [pixel][channel], PITCH bytes
 // a pixel (16 more than the channels need: neighbouring pixels' 16-byte
 // pieces then fall on different banks).
-template <int WM, int TN, int CB, int TW_, int S, int D>
+template <int WM, int MB, int TN, int CB, int TW_, int S, int D>
 struct MGeo {
-  static constexpr int WN = 4 / WM, BM = 64 * WM, NBLK = WN * TN, BN = 32 * NBLK;
+  static constexpr int WN = 4 / WM, BM = 32 * MB * WM, NBLK = WN * TN, BN = 32 * NBLK;
   static constexpr int TW = TW_, TH = BN / TW, RPB = 32 / TW;   // rows of a 32-pixel block
   static constexpr int HR = (TH - 1) * S + 2 * D + 1;
   static constexpr int HC = ((TW - 1) * S + 2 * D + 1 + 1 + 1) / 2 * 2;   // from an even column: one more, even
@@ -126,7 +126,14 @@ struct MGeo {
 // is read from memory once, transposed in registers (8 channels of a pixel
 // pair: eight 4-byte loads, eight byte permutes, two 16-byte LDS writes) and
 // read by all nine taps as shifted 16-byte LDS reads.  The weights never
-// touch LDS: they lie in memory in operand order (one contiguous KB per 32
+// touch LDS: every wave reads its own filters', so a k-step costs a unit's
+// cache 4 MB KB.  The 64 x 128 tile therefore takes one block of filters by
+// two of pixels per wave (with two by one, all four waves read the same
+// filters: bound by that cache at 43 of its 64 B per clock, also with four
+// times the waves; 512 -> 512 at 14 x 14 28.7 -> 22.3, 256 -> 256 at 56 x 56
+// 17.4 -> 14.0, 64 -> 64 at 224 x 224 12.6 -> 9.9, 512 -> 512 stride 2 at 32 x
+// 32 41.8 -> 36.4), its pixel operands read two k-steps ahead (3 % of those).
+// They lie in memory in operand order (one contiguous KB per 32
 // filters x 16 k), so each operand is one coalesced 16-byte load per lane,
 // issued PF k-steps ahead; k runs channel block by channel block of 16, tap
 // by tap inside.  Measured (bf16, us, per-tap gather -> this): 64 -> 64 at
@@ -139,12 +146,13 @@ struct MGeo {
 // PX2: the halo is staged by pixel pairs (even image width, no upsample),
 // else pixel by pixel; with PP_UPSAMPLE2 the conv's input is the nearest x2
 // upsampling of x.
-template <int WM, int TN, int CB, int TW_, int S, int D, bool PX2>
+template <int WM, int MB, int TN, int CB, int TW_, int S, int D, bool PX2>
 __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, const uint16_t* __restrict__ am,
                                                                const float* __restrict__ bias, MTiles mt) {
-  using M = MGeo<WM, TN, CB, TW_, S, D>;
+  using M = MGeo<WM, MB, TN, CB, TW_, S, D>;
   constexpr int KS = CB / 16 * 9;        // k-steps (16 deep) of a channel block
   constexpr int PF = TN < 4 && KS % 6 == 0 ? 6 : 3;   // weights in flight ahead, in k-steps (divides KS)
+  constexpr int BD = MB == 1 ? 2 : 1;    // pixel operands read ahead, in k-steps
   constexpr int PW = PX2 ? 2 : 1;        // pixels per staged item
   constexpr int NPC = M::HC / PW;        // items across
   constexpr int ITEMS = NPC * M::HR * (CB / 8);
@@ -227,10 +235,10 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
   // R = min(32, c_out - 32 mb) rows; a row past them reads zero
   const __amdgpu_buffer_rsrc_t arsrc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(am), static_cast<short>(0), a.c_out * 9 * a.c_in * 2, 0x00020000);
-  uint32_t aoff[2], astep[2];
+  uint32_t aoff[MB], astep[MB];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int mb = mtile * (M::BM / 32) + wm * 2 + i;
+  for (int i = 0; i < MB; ++i) {
+    const int mb = mtile * (M::BM / 32) + wm * MB + i;
     const int rows = min(32, a.c_out - 32 * mb);
     const int row = lane & 31;
     aoff[i] = row < rows ? static_cast<uint32_t>(mb) * 32u * 18u * a.c_in + ((lane >> 5) * rows + row) * 16u : kOut;
@@ -239,10 +247,10 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
   const int nblk = a.c_in / CB;
   const uint32_t last_step = static_cast<uint32_t>(nblk) * KS - 1;
   typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
-  u32x4v ar[PF][2];
+  u32x4v ar[PF][MB];
   auto load_a = [&](int slot, uint32_t step) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MB; ++i)
       ar[slot][i] = __builtin_bit_cast(
           u32x4v, __builtin_amdgcn_raw_buffer_load_b128(arsrc, aoff[i], static_cast<int>(step * astep[i]), 0));
   };
@@ -252,9 +260,9 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
   const int prow = wn * TN * M::RPB + lp / M::TW, pcol = lp % M::TW;
   const uint32_t lbase = (prow * S * M::HC + pcol * S + sh) * M::PITCH + (lane >> 5) * 16;
 
-  f32x16 acc[2][TN];
+  f32x16 acc[MB][TN];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < MB; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x16{};
 
@@ -274,21 +282,22 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
         for (int j = 0; j < TN; ++j)
           bv[j] = *reinterpret_cast<const bf16x8*>(bsrc + ((ky * D + j * M::RPB * S) * M::HC + kx * D) * M::PITCH + h * 32);
       };
-      bf16x8 bv[2][TN];
-      read_b(0, bv[0]);
+      bf16x8 bv[BD + 1][TN];
+#pragma unroll
+      for (int s = 0; s < BD; ++s) read_b(s, bv[s]);
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
         // (loads return in order: issued any earlier, the next block's input would hold up the weights behind it)
         if (s == KS - PF && more) fetch(cb + 1);
-        if (s + 1 < KS) read_b(s + 1, bv[(s + 1) & 1]);
-        bf16x8 av[2];
+        if (s + BD < KS) read_b(s + BD, bv[(s + BD) % (BD + 1)]);
+        bf16x8 av[MB];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) av[i] = __builtin_bit_cast(bf16x8, ar[s % PF][i]);
+        for (int i = 0; i < MB; ++i) av[i] = __builtin_bit_cast(bf16x8, ar[s % PF][i]);
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < MB; ++i)
 #pragma unroll
           for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bv[s & 1][j], acc[i][j], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bv[s % (BD + 1)][j], acc[i][j], 0, 0, 0);
         // the ring's next k-step (past the last one that one again: nothing outside the weights is read)
         const int ns = s + PF;
         load_a(s % PF, min(static_cast<uint32_t>(cb * KS + ns), last_step));
@@ -306,7 +315,7 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
   // (NaN stays; a false alarm only costs the look), 0.5 % of a 128 x 256 tile.
   float probe = 0.0f;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < MB; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -314,7 +323,7 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
   if (__any(probe != probe)) {
     const uint16_t* xi = static_cast<const uint16_t*>(a.x) + static_cast<size_t>(img) * a.c_in * hw;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         const int oy = oy0 + prow + j * M::RPB, ox = ox0 + pcol;
@@ -326,7 +335,7 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
         while (bad) {
           const int r = __builtin_ctz(bad);
           bad &= bad - 1;
-          const int o = mtile * M::BM + (wm * 2 + i) * 32 + 8 * (r >> 2) + (lane >> 5) * 4 + (r & 3);
+          const int o = mtile * M::BM + (wm * MB + i) * 32 + 8 * (r >> 2) + (lane >> 5) * 4 + (r & 3);
           if (o >= a.c_out) continue;
           const int rows = min(32, a.c_out - (o & ~31));
           const uint16_t* wp = am + static_cast<size_t>(o >> 5) * 32 * 9 * a.c_in + (o & 31) * 8;
@@ -354,9 +363,9 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
   const size_t plane = static_cast<size_t>(a.ho) * a.wo;
   uint16_t* __restrict__ y = static_cast<uint16_t*>(a.y) + static_cast<size_t>(img) * a.c_out * plane;
   const uint32_t half4 = (lane >> 5) * 4, odd = lane & 1;
-  const int ob = mtile * M::BM + wm * 64;   // the wave's first filter
+  const int ob = mtile * M::BM + wm * MB * 32;   // the wave's first filter
   auto act2 = [&](int i, int j, int r) __attribute__((always_inline)) -> uint32_t {   // rows r, r + 1, in bf16
-    const int ol = (wm * 2 + i) * 32 + 8 * (r >> 2) + half4 + (r & 3);
+    const int ol = (wm * MB + i) * 32 + 8 * (r >> 2) + half4 + (r & 3);
     float v0 = acc[i][j][r] + bias_s[ol], v1 = acc[i][j][r + 1] + bias_s[ol + 1];
     if (relu) {
       v0 = fmaxf(v0, 0.0f);
@@ -374,7 +383,7 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
       if (ey >= a.ho || ex >= a.wo) continue;
       const uint32_t voff = (half4 * static_cast<uint32_t>(plane) + (2u * ey) * 2u * a.wo + 2u * ex) * 2u;
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int r = 0; r < 16; r += 2) {
           const int os = ob + 32 * i + 8 * (r >> 2);   // multiple of 8
@@ -395,7 +404,7 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
       const bool valid = ey < a.ho && ex < a.wo;
       const uint32_t voff = ((half4 + odd) * static_cast<uint32_t>(plane) + static_cast<uint32_t>(ey) * a.wo + ex - odd) * 2u;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < MB; ++i) {
         auto at = [&](int r) __attribute__((always_inline)) {
           return reinterpret_cast<uint32_t*>(
               reinterpret_cast<uint8_t*>(y + static_cast<size_t>(ob + 32 * i + 8 * (r >> 2) + (r & 3)) * plane) + voff);
@@ -428,7 +437,7 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
     if (ey >= a.ho || ex >= a.wo) continue;
     const uint32_t voff = (half4 * static_cast<uint32_t>(plane) + static_cast<uint32_t>(ey) * a.wo + ex) * 2u;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
       for (int r = 0; r < 16; r += 2) {
         const uint32_t u = act2(i, j, r);
@@ -462,7 +471,10 @@ long tiles(const ConvParams& p, int bm, int th, int tw) {
 //   64 x 256 for at most 64 filters from 400 (64 -> 64 at 270 x 480: 18, 64 x 128 21)
 //   64 x 128 below (128 -> 128 at 128 x 128: 12.3, 128 x 128 14)
 // 128 x 128 stages 64 channels at a time when c_in is a multiple of 64 (one workgroup per
-// unit: half the waits for a block's input; 512 -> 512: 37 against 39).  The
+// unit: half the waits for a block's input; 512 -> 512: 37 against 39), and
+// 64 x 128 does from 128 channels on grids of at most one workgroup per unit
+// (512 -> 512 at 28 x 28 26.2 against 27.9; 64 -> 64 with dilation 2 at 256 x 256 14.7
+// against 11.8: not below, where two workgroups per unit come first).  The
 // 128-pixel tiles are 4 x 32 or 8 x 16 outputs, whichever covers the map with fewer tiles.
 // Every tile sums in the same order: the choice never changes a result's bits.
 enum Form { kS2, kS2Wide, k128x256, k64x256, k128x128, k64x128 };
@@ -477,9 +489,9 @@ Form choose_form(const ConvParams& p) {
   return wide && std::min(tiles(p, 128, 8, 16), tiles(p, 128, 4, 32)) >= 192 ? k128x128 : k64x128;
 }
 
-template <int WM, int TN, int CB, int TW, int S, int D>
+template <int WM, int MB, int TN, int CB, int TW, int S, int D>
 hipError_t launch_tiles(const ConvParams& p, const uint16_t* am, const float* bo, hipStream_t st) {
-  using M = MGeo<WM, TN, CB, TW, S, D>;
+  using M = MGeo<WM, MB, TN, CB, TW, S, D>;
   static_assert(M::LDS + M::BM * 4 <= 160 * 1024, "staging buffers fit the LDS");
   MTiles t;
   t.m_tiles = (p.c_out + M::BM - 1) / M::BM;
@@ -491,9 +503,9 @@ hipError_t launch_tiles(const ConvParams& p, const uint16_t* am, const float* bo
   // pixel pairs: rows of whole 4-byte words (an upsampled input reads each stored pixel twice)
   const bool px2 = p.w % 2 == 0 && !(p.flags & PP_UPSAMPLE2) && reinterpret_cast<uintptr_t>(p.x) % 4 == 0;
   if (px2)
-    hipLaunchKernelGGL((pp_mfma_conv_kernel<WM, TN, CB, TW, S, D, true>), grid, dim3(256), 0, st, p, am, bo, t);
+    hipLaunchKernelGGL((pp_mfma_conv_kernel<WM, MB, TN, CB, TW, S, D, true>), grid, dim3(256), 0, st, p, am, bo, t);
   else
-    hipLaunchKernelGGL((pp_mfma_conv_kernel<WM, TN, CB, TW, S, D, false>), grid, dim3(256), 0, st, p, am, bo, t);
+    hipLaunchKernelGGL((pp_mfma_conv_kernel<WM, MB, TN, CB, TW, S, D, false>), grid, dim3(256), 0, st, p, am, bo, t);
   return hipGetLastError();
 }
 
@@ -515,16 +527,16 @@ bool mfma_eligible(const ConvParams& p) {
 // A workgroup's time is linear in c_in (what bounds it is the weights' way
 // through its unit's cache, the same for every channel), and workgroups past
 // one per unit queue.  us per input channel, measured on MI355X: 64 x 128
-// 0.0455 (512 -> 512 at 14 x 14 28.1, 256 -> 256 at 20 x 30 16.8, 64 -> 64 at
-// 224 x 224, 392 tiles, 12.1), 128 x 128 0.0625 (512 -> 512 on 8 x 32 x 32
+// 0.036 (512 -> 512 at 14 x 14 21.2, 256 -> 256 at 56 x 56 13.4, 64 -> 64 at
+// 224 x 224, 392 tiles, 9.9), 128 x 128 0.0625 (512 -> 512 on 8 x 32 x 32
 // 37), 64 x 256 0.105, 128 x 256 0.16 (64 -> 256 at 540 x 960 170), stride 2
-// 0.072 (512 -> 512 at 32 x 32 41.5), its 128 x 128 0.1; 5 us to launch, fill
+// 0.062 (512 -> 512 at 32 x 32 36.4), its 128 x 128 0.1; 5 us to launch, fill
 // and drain.
 double mfma_time(const ConvParams& p) {
-  double us = 0.0455;
+  double us = 0.036;
   long t = std::min(tiles(p, 64, 8, 16), tiles(p, 64, 4, 32));
   switch (choose_form(p)) {
-    case kS2: us = 0.072, t = tiles(p, 64, 4, 32); break;
+    case kS2: us = 0.062, t = tiles(p, 64, 4, 32); break;
     case kS2Wide: us = 0.1, t = tiles(p, 128, 4, 32); break;
     case k128x256: us = 0.16, t = tiles(p, 128, 8, 32); break;
     case k64x256: us = 0.105, t = tiles(p, 64, 8, 32); break;
@@ -556,21 +568,25 @@ hipError_t launch_mfma_conv(const ConvParams& p, hipStream_t st) {
   }
   const bool d1 = p.dil == 1;
   switch (choose_form(p)) {
-    case kS2: return d1 ? launch_tiles<1, 1, 16, 32, 2, 1>(p, am, bo, st) : launch_tiles<1, 1, 16, 32, 2, 2>(p, am, bo, st);
-    case kS2Wide: return launch_tiles<2, 2, 32, 32, 2, 1>(p, am, bo, st);
-    case k128x256: return launch_tiles<2, 4, 32, 32, 1, 1>(p, am, bo, st);
-    case k64x256: return launch_tiles<1, 2, 32, 32, 1, 1>(p, am, bo, st);
+    case kS2: return d1 ? launch_tiles<2, 1, 2, 16, 32, 2, 1>(p, am, bo, st) : launch_tiles<2, 1, 2, 16, 32, 2, 2>(p, am, bo, st);
+    case kS2Wide: return launch_tiles<2, 2, 2, 32, 32, 2, 1>(p, am, bo, st);
+    case k128x256: return launch_tiles<2, 2, 4, 32, 32, 1, 1>(p, am, bo, st);
+    case k64x256: return launch_tiles<1, 2, 2, 32, 32, 1, 1>(p, am, bo, st);
     case k128x128:
       if (p.c_in % 64 == 0) {
-        if (is_tall(p)) return d1 ? launch_tiles<2, 2, 64, 16, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 64, 16, 1, 2>(p, am, bo, st);
-        return d1 ? launch_tiles<2, 2, 64, 32, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 64, 32, 1, 2>(p, am, bo, st);
+        if (is_tall(p)) return d1 ? launch_tiles<2, 2, 2, 64, 16, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 2, 64, 16, 1, 2>(p, am, bo, st);
+        return d1 ? launch_tiles<2, 2, 2, 64, 32, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 2, 64, 32, 1, 2>(p, am, bo, st);
       }
-      if (is_tall(p)) return d1 ? launch_tiles<2, 2, 32, 16, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 32, 16, 1, 2>(p, am, bo, st);
-      return d1 ? launch_tiles<2, 2, 32, 32, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 32, 32, 1, 2>(p, am, bo, st);
+      if (is_tall(p)) return d1 ? launch_tiles<2, 2, 2, 32, 16, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 2, 32, 16, 1, 2>(p, am, bo, st);
+      return d1 ? launch_tiles<2, 2, 2, 32, 32, 1, 1>(p, am, bo, st) : launch_tiles<2, 2, 2, 32, 32, 1, 2>(p, am, bo, st);
     case k64x128: break;
   }
-  if (is_tall(p)) return d1 ? launch_tiles<1, 1, 32, 16, 1, 1>(p, am, bo, st) : launch_tiles<1, 1, 32, 16, 1, 2>(p, am, bo, st);
-  return d1 ? launch_tiles<1, 1, 32, 32, 1, 1>(p, am, bo, st) : launch_tiles<1, 1, 32, 32, 1, 2>(p, am, bo, st);
+  if (p.c_in % 64 == 0 && p.c_in >= 128 && tiles(p, 64, is_tall(p) ? 8 : 4, is_tall(p) ? 16 : 32) <= 256) {
+    if (is_tall(p)) return d1 ? launch_tiles<2, 1, 2, 64, 16, 1, 1>(p, am, bo, st) : launch_tiles<2, 1, 2, 64, 16, 1, 2>(p, am, bo, st);
+    return d1 ? launch_tiles<2, 1, 2, 64, 32, 1, 1>(p, am, bo, st) : launch_tiles<2, 1, 2, 64, 32, 1, 2>(p, am, bo, st);
+  }
+  if (is_tall(p)) return d1 ? launch_tiles<2, 1, 2, 32, 16, 1, 1>(p, am, bo, st) : launch_tiles<2, 1, 2, 32, 16, 1, 2>(p, am, bo, st);
+  return d1 ? launch_tiles<2, 1, 2, 32, 32, 1, 1>(p, am, bo, st) : launch_tiles<2, 1, 2, 32, 32, 1, 2>(p, am, bo, st);
 }
 
 }  // namespace pp

@@ -316,3 +316,20 @@ def test_mfma_infinities_reach_kept_taps_only(case, monkeypatch):
     assert torch.equal(y[~fin].nan_to_num(nan=7.0), ref[~fin].nan_to_num(nan=7.0))
     # (both round an fp32 sum once: a bf16 ulp apart at most)
     assert torch.all((y[fin] - ref[fin]).abs() <= 2 ** -7 * ref[fin].abs() + 1e-5)
+
+
+@pytest.mark.parametrize("case", [  # (pad = dilation), (n, c_out, c_in, h, w): 64 x 128 tiles staged 64 channels at a time
+    (1, (1, 100, 128, 9, 17)),      # 8 x 16 tiles, ragged
+    (1, (1, 65, 192, 5, 34)),       # 4 x 32 tiles, three blocks, a filter in the second tile
+    (2, (2, 40, 128, 17, 33)),      # dilation 2, odd width
+    (2, (1, 64, 128, 9, 15)),
+])
+def test_mfma_64_channel_blocks(case, monkeypatch):
+    monkeypatch.setenv("PP_RECIPE", str(MFMA))
+    d, (n, c_out, c_in, h, w) = case
+    L, layer = _layer(1500, c_out, c_in, "canon8", 0.4, 1, d, d)
+    x = obf16.round_f32(workloads.random_input(1500, (n, c_in, h, w)))
+    _say("mfma 64-channel blocks", case)
+    y = _host(pp.conv2d_fwd(layer, _dev(x), relu=True))
+    ref, bound = _oracle(L, x, 1, d, d, True)
+    check(y, ref, bound, "bf16", f"mfma 64-channel blocks {case}")
