@@ -270,7 +270,7 @@ ConvPlan plan_conv(const ConvParams& p, int lib, bool bf16, bool allow_split, bo
   if (lib == kLibGeneric && !no_lean && p.c_in > 8) {
     // any other library: the mask-testing lean kernel, 2 x 4 outputs per lane
     // with 8 waves, on small maps 2 x 2 with 16 (column-pruned, fp32:
-    // 128 -> 128 at 128 x 128 55 us, 2 x 2 82, 176 on the channel-chunk
+    // 128 -> 128 at 128 x 128 48 us, 2 x 2 82, 189 on the channel-chunk
     // kernel; 64 -> 64 at 100 x 100 19, 26, 96, at 40 x 40 18, 13, 63)
     const bool small = pix < 64L * 64L;
     ConvPlan pl;

@@ -175,7 +175,7 @@ __device__ __forceinline__ void read_row_bf(float (&d)[PC], const uint8_t* rb) {
 // lane), both read with v_readlane.  Column pruning gives a channel the same
 // mask in every filter: its 9 tap tests then serve all 8 slots, so a step is
 // nearly all FMAs (VALU-bound: 128 -> 128 at 128 x 128, half the columns kept,
-// fp32, 55 us = 44 TFLOP/s against 176 on the channel-chunk kernel); any other
+// fp32, 48 us = 51 TFLOP/s against 189 on the channel-chunk kernel); any other
 // channel tests each kept slot's taps in turn.
 template <int R, int CC, int LW, int WS, bool V4, bool BF = false, bool PW = false, int D = 1, int S = 1, bool GEN = false>
 __global__ __launch_bounds__(WS * 64) void pp_conv3x3_lean_kernel(LeanParams a) {
