@@ -262,6 +262,24 @@ pp_status pp_conv2d_fwd_noalloc(const void* h_blob, size_t blob_bytes, const voi
                                 int32_t act_dtype, uint32_t flags, void* hip_stream);
 
 /*
+ * pp_conv2d_fwd_prepared -- pp_conv2d_fwd with the layer's prepared weights
+ * (written by pp_conv2d_prepare) in a buffer of their own, read where they
+ * lie by any number of calls and streams, beside an optional workspace:
+ *   prepared, prepared_bytes  that buffer, 256-byte aligned, read only
+ *   workspace, ws_bytes       as pp_conv2d_fwd; pp_conv2d_scratch with
+ *                             PP_PREPARED says what the call can use
+ * The plan and the result are those of pp_conv2d_fwd with PP_PREPARED.
+ * Errors: as pp_conv2d_fwd; PP_EINVAL also for PP_PREPARED in flags and a
+ * NULL or misaligned prepared, PP_ESIZE (prepared smaller than
+ * pp_conv2d_prepare writes).
+ */
+pp_status pp_conv2d_fwd_prepared(const void* h_blob, size_t blob_bytes, const void* d_blob,
+                                 const void* prepared, size_t prepared_bytes,
+                                 const void* x, void* y, int32_t n, int32_t h, int32_t w,
+                                 int32_t act_dtype, uint32_t flags, void* workspace, size_t ws_bytes,
+                                 void* hip_stream);
+
+/*
  * pp_conv2d_prepare -- write, once, a layer's weights in the form its
  * kernels read them, which pp_conv2d_fwd otherwise re-derives from the blob
  * on every call, in up to two parts.  The matrix-core part (bf16 layers
@@ -305,6 +323,16 @@ pp_status pp_conv2d_prepare(const void* h_blob, size_t blob_bytes, const void* d
  */
 pp_status pp_conv2d_workspace(const void* h_blob, size_t blob_bytes, int32_t n, int32_t h,
                               int32_t w, int32_t act_dtype, size_t* bytes);
+
+/*
+ * pp_conv2d_scratch -- the same for one call: the scratch bytes that
+ * pp_conv2d_fwd with these arguments and flags can use (h, w: of x as
+ * stored, also with PP_UPSAMPLE2), and with PP_PREPARED those that
+ * pp_conv2d_fwd_prepared can use beside the prepared weights (pp_conv2d_fwd:
+ * behind them).  Host-only.  Errors: as pp_conv2d_workspace.
+ */
+pp_status pp_conv2d_scratch(const void* h_blob, size_t blob_bytes, int32_t n, int32_t h, int32_t w,
+                            int32_t act_dtype, uint32_t flags, size_t* bytes);
 
 /*
  * pp_conv2d_recipe -- the GPU tiling ("recipe" id) and the channel split

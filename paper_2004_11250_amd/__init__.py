@@ -34,7 +34,7 @@ SYMBOLS = ("pp_pack", "pp_blob_info", "pp_conv2d_fwd", "pp_conv2d_workspace", "p
            "pp_conv2d_out_size", "pp_net_workspace", "pp_net_fwd", "pp_status_str", "pp_last_error",
            "pp_project_patterns", "pp_project_connectivity", "pp_project_columns", "pp_column_library",
            "pp_fold_bn", "pp_jit_library", "pp_conv2d_fwd_noalloc", "pp_net_plan", "pp_round_bf16",
-           "pp_conv2d_prepare")
+           "pp_conv2d_prepare", "pp_conv2d_fwd_prepared", "pp_conv2d_scratch")
 
 
 class PPError(RuntimeError):
@@ -76,7 +76,9 @@ def load_library(path: str = LIB_PATH):
         "pp_conv2d_fwd": [vp, sz, vp, vp, vp, i32, i32, i32, i32, u32, vp, sz, vp],
         "pp_conv2d_fwd_noalloc": [vp, sz, vp, vp, vp, i32, i32, i32, i32, u32, vp],
         "pp_conv2d_workspace": [vp, sz, i32, i32, i32, i32, ctypes.POINTER(sz)],
+        "pp_conv2d_scratch": [vp, sz, i32, i32, i32, i32, u32, ctypes.POINTER(sz)],
         "pp_conv2d_prepare": [vp, sz, vp, vp, ctypes.POINTER(sz), vp],
+        "pp_conv2d_fwd_prepared": [vp, sz, vp, vp, sz, vp, vp, i32, i32, i32, i32, u32, vp, sz, vp],
         "pp_conv2d_out_size": [vp, sz, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)],
         "pp_conv2d_recipe": [vp, sz, i32, i32, i32, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)],
         "pp_net_workspace": [ctypes.POINTER(NetOp), i32, i32, i32, i32, i32, i32, ctypes.POINTER(sz),
@@ -280,6 +282,12 @@ def _stream_ptr(stream=None) -> int:
     return int(s.cuda_stream)
 
 
+def _capturing(stream) -> bool:
+    torch = _torch()
+    with torch.cuda.stream(stream):
+        return torch.cuda.is_current_stream_capturing()
+
+
 class PackedLayer:
     """A packed layer: host copy (for header parsing) + device copy."""
 
@@ -298,8 +306,9 @@ class PackedLayer:
         device buffer kept on the layer (bf16: the matrix-core form's; fp32
         canonical-library stride-1 layers: the lean kernel's expanded
         weights; conv2d_fwd(..., prepared=True) then skips the per-call
-        expansion).  Returns the buffer, or None for a layer none of those
-        forms runs."""
+        expansion).  Waits until it is written, so that calls on any stream
+        may read it (under graph capture it is written when the graph runs).
+        Returns the buffer, or None for a layer none of those forms runs."""
         torch = _torch()
         lib = load_library()
         nb = ctypes.c_size_t(0)
@@ -312,6 +321,9 @@ class PackedLayer:
             raise RuntimeError("prepared-weights allocation is not 256-byte aligned")
         _check(lib.pp_conv2d_prepare(_ptr(self.h_blob), self.h_blob.nbytes, self.d_blob.data_ptr(), buf.data_ptr(),
                                      ctypes.byref(nb), _stream_ptr(stream)), "pp_conv2d_prepare")
+        on = torch.cuda.ExternalStream(_stream_ptr(stream))
+        if not _capturing(on):
+            on.synchronize()
         self.prepared = buf
         return buf
 
@@ -350,6 +362,13 @@ class PackedLayer:
                "pp_conv2d_workspace")
         return b.value
 
+    def _scratch_bytes(self, n, h, w, act_dtype, flags) -> int:
+        """Scratch bytes of a call (pp_conv2d_scratch; asked every call, as above)."""
+        b = ctypes.c_size_t(0)
+        _check(load_library().pp_conv2d_scratch(self._h_ptr, self._h_blob.nbytes, n, h, w, act_dtype, flags,
+                                                ctypes.byref(b)), "pp_conv2d_scratch")
+        return b.value
+
     @classmethod
     def from_weights(cls, w, b, pattern_id, conn, lib_masks, stride=1, pad=1, dilation=1, wdtype=PP_F32,
                      device="cuda"):
@@ -365,10 +384,8 @@ def conv2d_fwd(layer: PackedLayer, x, relu=False, out=None, stream=None, workspa
     accumulate: add the activated output to ``out`` in place (PP_ACCUMULATE;
     out is required).  pixshuf2: store through PixelShuffle(2)
     (PP_PIXSHUF2).  upsample2: convolve the nearest x2 upsampling of x
-    (PP_UPSAMPLE2).  prepared: pass the layer's prepared weights
-    (layer.prepare()) at the head of the workspace with PP_PREPARED; when
-    the layer can also use split scratch, a copy of them is kept (per input
-    shape) at the head of a buffer whose tail is that scratch."""
+    (PP_UPSAMPLE2).  prepared: read the layer's prepared weights
+    (layer.prepare()) where they lie, beside scratch as for "auto"."""
     torch = _torch()
     lib = load_library()
     if prepared and layer.prepared is None:
@@ -393,19 +410,10 @@ def conv2d_fwd(layer: PackedLayer, x, relu=False, out=None, stream=None, workspa
         out = x.new_empty(shape)
     elif tuple(out.shape) != shape or out.dtype != x.dtype or not out.is_contiguous():
         raise ValueError(f"out must be a contiguous {x.dtype} tensor of shape {shape}")
-    if prepared:
-        nb = layer._workspace(n, hc, wc, dt)
-        workspace = layer.prepared
-        if nb:
-            key = ("prepared", n, hc, wc, dt, x.device.index)
-            head = -(-layer.prepared.numel() // 256) * 256
-            workspace = layer.scratch.get(key)
-            if workspace is None or workspace.numel() < head + nb:
-                workspace = torch.empty(head + nb, dtype=torch.uint8, device=x.device)
-                workspace[:layer.prepared.numel()].copy_(layer.prepared)
-                layer.scratch[key] = workspace
-    elif isinstance(workspace, str) and workspace == "auto":
-        nb = layer._workspace(n, hc, wc, dt)
+    flags = ((PP_RELU if relu else 0) | (PP_MAXPOOL2 if maxpool2 else 0) | (PP_ACCUMULATE if accumulate else 0) |
+             (PP_PIXSHUF2 if pixshuf2 else 0) | (PP_UPSAMPLE2 if upsample2 else 0))
+    if prepared or (isinstance(workspace, str) and workspace == "auto"):
+        nb = layer._scratch_bytes(n, h, w, dt, flags | PP_PREPARED) if prepared else layer._workspace(n, hc, wc, dt)
         key = (n, hc, wc, dt, x.device.index)
         workspace = layer.scratch.get(key)
         if nb and (workspace is None or workspace.numel() < nb):
@@ -414,12 +422,12 @@ def conv2d_fwd(layer: PackedLayer, x, relu=False, out=None, stream=None, workspa
         if not nb:
             workspace = None
     ws_ptr, ws_bytes = (workspace.data_ptr(), workspace.numel()) if workspace is not None else (None, 0)
-    st = lib.pp_conv2d_fwd(layer._h_ptr, layer._h_blob.nbytes, layer.d_blob.data_ptr(), x.data_ptr(),
-                           out.data_ptr(), n, h, w, dt,
-                           (PP_RELU if relu else 0) | (PP_MAXPOOL2 if maxpool2 else 0) |
-                           (PP_ACCUMULATE if accumulate else 0) | (PP_PIXSHUF2 if pixshuf2 else 0) |
-                           (PP_UPSAMPLE2 if upsample2 else 0) | (PP_PREPARED if prepared else 0), ws_ptr, ws_bytes,
-                           _stream_ptr(stream))
+    args = (x.data_ptr(), out.data_ptr(), n, h, w, dt, flags, ws_ptr, ws_bytes, _stream_ptr(stream))
+    if prepared:
+        st = lib.pp_conv2d_fwd_prepared(layer._h_ptr, layer._h_blob.nbytes, layer.d_blob.data_ptr(),
+                                        layer.prepared.data_ptr(), layer.prepared.numel(), *args)
+    else:
+        st = lib.pp_conv2d_fwd(layer._h_ptr, layer._h_blob.nbytes, layer.d_blob.data_ptr(), *args)
     _check(st, "pp_conv2d_fwd")
     return out
 

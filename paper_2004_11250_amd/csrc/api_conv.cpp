@@ -204,11 +204,31 @@ bool conv_fusable(const BlobView& v, int32_t n, int32_t h, int32_t w, int32_t ac
   return true;
 }
 
-size_t conv_scratch_bytes(const BlobView& v, int32_t n, int32_t h, int32_t w, int32_t act_dtype) {
+// (the matrix-core form's scratch is its expanded weights: none when prepared)
+static size_t plan_scratch(const ConvPlan& pl, const ConvParams& p, uint32_t flags) {
+  if (pl.recipe < 0 || (pl.recipe == kRecipeMfma && (flags & PP_PREPARED))) return 0;
+  return split_bytes(pl, p);
+}
+
+size_t conv_scratch_bytes(const BlobView& v, int32_t n, int32_t h, int32_t w, int32_t act_dtype, uint32_t flags) {
   int ho = 0, wo = 0;
   if (conv_check(v, n, h, w, act_dtype, &ho, &wo) != PP_OK) return 0;
-  const ConvParams p = layer_params(v, n, h, w, ho, wo);
-  return split_bytes(plan_conv(p, library_kind(v), act_dtype == PP_BF16, true), p);
+  ConvParams p = layer_params(v, n, h, w, ho, wo);
+  p.flags = flags & ~static_cast<uint32_t>(PP_PREPARED);
+  return plan_scratch(plan_conv(p, library_kind(v), act_dtype == PP_BF16, true), p, flags);
+}
+
+// the same, also covering run-time compiled kernels' plan
+static size_t call_scratch_bytes(const BlobView& v, int32_t n, int32_t h, int32_t w, int32_t act_dtype, uint32_t flags) {
+  size_t bytes = conv_scratch_bytes(v, n, h, w, act_dtype, flags);
+  int ho = 0, wo = 0;
+  if (library_kind(v) == kLibGeneric && jit_library4(v) && conv_check(v, n, h, w, act_dtype, &ho, &wo) == PP_OK) {
+    ConvParams p = layer_params(v, n, h, w, ho, wo);
+    p.flags = flags & ~static_cast<uint32_t>(PP_PREPARED);
+    const size_t b = plan_scratch(plan_conv(p, kLibCanon8, act_dtype == PP_BF16, true, true), p, flags);
+    if (b > bytes) bytes = b;
+  }
+  return bytes;
 }
 
 // launch parameters of one layer for an n x c_in x h x w input (device
@@ -314,13 +334,24 @@ extern "C" pp_status pp_conv2d_workspace(const void* h_blob, size_t blob_bytes, 
   int ho = 0, wo = 0;
   s = conv_check(v, n, h, w, act_dtype, &ho, &wo);
   if (s != PP_OK) return s;
-  *bytes = conv_scratch_bytes(v, n, h, w, act_dtype);
-  if (library_kind(v) == kLibGeneric && jit_library4(v)) {
-    // enough for the canonical plan that run-time compiled kernels run
-    const ConvParams p = layer_params(v, n, h, w, ho, wo);
-    const size_t b = split_bytes(plan_conv(p, kLibCanon8, act_dtype == PP_BF16, true, true), p);
-    if (b > *bytes) *bytes = b;
-  }
+  *bytes = call_scratch_bytes(v, n, h, w, act_dtype, 0);
+  return PP_OK;
+}
+
+extern "C" pp_status pp_conv2d_scratch(const void* h_blob, size_t blob_bytes, int32_t n, int32_t h, int32_t w,
+                                       int32_t act_dtype, uint32_t flags, size_t* bytes) {
+  clear_error();
+  BlobView v;
+  pp_status s = parse_blob(h_blob, blob_bytes, &v, /*full=*/false);
+  if (s != PP_OK) return s;
+  if (!bytes) return fail(PP_EINVAL, "bytes is NULL");
+  const bool up = (flags & PP_UPSAMPLE2) != 0;
+  if (up && (h < 1 || w < 1 || h > (1 << 29) || w > (1 << 29))) return fail(PP_EINVAL, "bad h, w");
+  const int hv = up ? 2 * h : h, wv = up ? 2 * w : w;
+  int ho = 0, wo = 0;
+  s = conv_check(v, n, hv, wv, act_dtype, &ho, &wo);
+  if (s != PP_OK) return s;
+  *bytes = call_scratch_bytes(v, n, hv, wv, act_dtype, flags);
   return PP_OK;
 }
 
@@ -401,4 +432,29 @@ extern "C" pp_status pp_conv2d_fwd(const void* h_blob, size_t blob_bytes, const 
   if (ws_bytes && !workspace) return fail(PP_EINVAL, "NULL workspace with nonzero size");
   return conv_enqueue(v, d_blob, x, y, n, h, w, act_dtype, flags, workspace, workspace ? ws_bytes : 0,
                       static_cast<hipStream_t>(hip_stream));
+}
+
+extern "C" pp_status pp_conv2d_fwd_prepared(const void* h_blob, size_t blob_bytes, const void* d_blob,
+                                            const void* prepared, size_t prepared_size, const void* x, void* y,
+                                            int32_t n, int32_t h, int32_t w, int32_t act_dtype, uint32_t flags,
+                                            void* workspace, size_t ws_bytes, void* hip_stream) {
+  clear_error();
+  BlobView v;
+  pp_status s = parse_blob(h_blob, blob_bytes, &v, /*full=*/false);
+  if (s != PP_OK) return s;
+  if (ws_bytes && !workspace) return fail(PP_EINVAL, "NULL workspace with nonzero size");
+  if (flags & PP_PREPARED) return fail(PP_EINVAL, "unknown flags");
+  if (!prepared || reinterpret_cast<uintptr_t>(prepared) % 256)
+    return fail(PP_EINVAL, "the prepared weights must be a 256-byte aligned device pointer");
+  if (prepared_size < prepared_bytes(v)) return fail(PP_ESIZE, "prepared weights smaller than pp_conv2d_prepare writes");
+  if ((flags & PP_UPSAMPLE2) && (h < 1 || w < 1 || h > (1 << 29) || w > (1 << 29))) return fail(PP_EINVAL, "bad h, w");
+  const hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  // the matrix-core form reads them as the head of a workspace that it does
+  // not write; any other plan takes the lean part (if there is one) and its
+  // split's scratch from the workspace
+  if (act_dtype == PP_BF16 && conv_recipe(v, n, h, w, act_dtype, flags, prepared_bytes(v)) == kRecipeMfma)
+    return conv_enqueue(v, d_blob, x, y, n, h, w, act_dtype, flags | PP_PREPARED, const_cast<void*>(prepared),
+                        prepared_bytes(v), st);
+  return conv_enqueue(v, d_blob, x, y, n, h, w, act_dtype, flags, workspace, workspace ? ws_bytes : 0, st,
+                      lean_prepared(v, prepared));
 }

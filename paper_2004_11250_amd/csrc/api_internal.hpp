@@ -53,7 +53,9 @@ int conv_recipe(const BlobView& v, int32_t n, int32_t h, int32_t w, int32_t act_
 size_t prepared_bytes(const BlobView& v);
 const void* lean_prepared(const BlobView& v, const void* prepared);
 
-// scratch bytes pp_conv2d_fwd can use for this layer and input (0: none)
-size_t conv_scratch_bytes(const BlobView& v, int32_t n, int32_t h, int32_t w, int32_t act_dtype);
+// scratch bytes a call can use for this layer and input (0: none); flags as
+// pp_conv2d_fwd (with PP_PREPARED beside the prepared weights); h, w: the
+// conv's input size (with PP_UPSAMPLE2 the upsampled size)
+size_t conv_scratch_bytes(const BlobView& v, int32_t n, int32_t h, int32_t w, int32_t act_dtype, uint32_t flags = 0);
 
 }  // namespace pp

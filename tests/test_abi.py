@@ -293,3 +293,38 @@ def test_prepare_host_checks(lib):
     # the allocation-free call has no prepared buffer to read
     assert lib.pp_conv2d_fwd_noalloc(blob.ctypes.data, blob.nbytes, 0x100000, 0x200000, 0x300000, 1, 8, 8,
                                      pp.PP_BF16, pp.PP_PREPARED, None) == pp.PP_EINVAL
+
+def test_prepared_entry_checks_on_the_host(lib):
+    # every call fails before anything is enqueued: the addresses are never touched
+    L = workloads.random_layer(3400, 40, 64, keep=0.5)
+    b = pp.pack(L["w"], L["b"], L["pid"], L["conn"], L["lib"], 1, 1, 1, pp.PP_BF16)
+    nb = ctypes.c_size_t(0)
+    assert lib.pp_conv2d_prepare(b.ctypes.data, b.nbytes, None, None, ctypes.byref(nb), None) == pp.PP_OK
+
+    def call(prepared=0x400000, size=nb.value, flags=0, h=16, d_blob=0x300000):
+        return lib.pp_conv2d_fwd_prepared(b.ctypes.data, b.nbytes, d_blob, prepared, size, 0x100000, 0x200000, 1, h, 16,
+                                          pp.PP_BF16, flags, None, 0, None)
+
+    assert call(prepared=None) == pp.PP_EINVAL and call(prepared=0x400010) == pp.PP_EINVAL
+    assert call(size=nb.value - 1) == pp.PP_ESIZE
+    assert call(flags=pp.PP_PREPARED) == pp.PP_EINVAL and call(flags=64) == pp.PP_EINVAL
+    assert call(h=0) == pp.PP_EINVAL and call(d_blob=0x300010) == pp.PP_EINVAL
+    assert call(h=1 << 30, flags=pp.PP_UPSAMPLE2) == pp.PP_EINVAL
+
+
+def test_scratch_of_a_prepared_call(lib):
+    def scratch(blob, n, h, w, dt, flags):
+        nb = ctypes.c_size_t(0)
+        assert lib.pp_conv2d_scratch(blob.ctypes.data, blob.nbytes, n, h, w, dt, flags, ctypes.byref(nb)) == pp.PP_OK
+        return nb.value
+
+    L = workloads.random_layer(3500, 256, 256, keep=1 / 3)
+    b = pp.pack(L["w"], L["b"], L["pid"], L["conn"], L["lib"], wdtype=pp.PP_BF16)
+    assert pp.conv2d_recipe(b, 1, 56, 56, pp.PP_BF16) == 64
+    assert scratch(b, 1, 56, 56, pp.PP_BF16, 0) == pp.conv2d_workspace(b, 1, 56, 56, pp.PP_BF16) > 0
+    assert scratch(b, 1, 56, 56, pp.PP_BF16, pp.PP_PREPARED) == 0     # the expanded weights are there
+    f = pp.pack(L["w"], L["b"], L["pid"], L["conn"], L["lib"])        # a channel split: partial sums all the same
+    assert scratch(f, 1, 14, 14, pp.PP_F32, pp.PP_PREPARED) == pp.conv2d_workspace(f, 1, 14, 14) > 0
+    assert lib.pp_conv2d_scratch(b.ctypes.data, b.nbytes, 1, 8, 8, pp.PP_BF16, 0, None) == pp.PP_EINVAL
+    nb = ctypes.c_size_t(0)
+    assert lib.pp_conv2d_scratch(b.ctypes.data, b.nbytes, 0, 8, 8, pp.PP_BF16, 0, ctypes.byref(nb)) == pp.PP_EINVAL

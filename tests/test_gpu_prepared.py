@@ -1,0 +1,83 @@
+"""Prepared weights are read where pp_conv2d_prepare wrote them, by calls on
+any stream: bitwise the result of the call that expands them itself, right
+after prepare(), after a second prepare() with other weights, and where the
+first prepared call of a shape is recorded in a graph."""
+import numpy as np
+import pytest
+
+import workloads
+from oracle import bf16 as obf16
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+pp = pytest.importorskip("paper_2004_11250_amd")
+
+SHAPES = [  # dtype, (n, c_out, c_in, h, w): the matrix-core form, and the lean kernel with and without a channel split
+    ("bf16", (1, 256, 256, 56, 56)),
+    ("bf16", (1, 512, 512, 14, 14)),
+    ("f32", (1, 512, 512, 14, 14)),
+    ("f32", (1, 64, 64, 60, 44)),
+]
+
+
+def _pair(seed, dtype, shape):
+    """(packed layer, input)"""
+    n, c_out, c_in, h, w = shape
+    L = workloads.random_layer(seed, c_out, c_in, keep=1 / 3)
+    wd = pp.PP_BF16 if dtype == "bf16" else pp.PP_F32
+    layer = pp.PackedLayer.from_weights(L["w"], L["b"], L["pid"], L["conn"], L["lib"], wdtype=wd)
+    x = torch.from_numpy(obf16.round_f32(workloads.random_input(seed, (n, c_in, h, w)))).cuda()
+    return layer, x.to(torch.bfloat16) if dtype == "bf16" else x
+
+
+@pytest.mark.parametrize("dtype,shape", SHAPES)
+def test_another_stream_right_after_prepare(dtype, shape):
+    layer, x = _pair(3100, dtype, shape)
+    print("prepared, another stream", dtype, shape, flush=True)
+    want = pp.conv2d_fwd(layer, x, relu=True)
+    out = torch.empty_like(want)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    layer.scratch.clear()
+    layer.prepare()
+    pp.conv2d_fwd(layer, x, relu=True, prepared=True, stream=side, out=out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
+    if pp.conv2d_recipe(layer.h_blob, shape[0], *shape[3:], layer.info["wdtype"]) == 64:
+        assert not layer.scratch   # no copy of the weights
+
+
+@pytest.mark.parametrize("dtype,shape", SHAPES)
+def test_second_prepare_with_other_weights(dtype, shape):
+    layer, x = _pair(3200, dtype, shape)
+    other, _ = _pair(3201, dtype, shape)
+    print("prepared twice", dtype, shape, flush=True)
+    layer.prepare()
+    first = pp.conv2d_fwd(layer, x, prepared=True)
+    layer.h_blob, layer.d_blob, layer.info = other.h_blob, other.d_blob, other.info
+    layer.prepare()
+    got, want = pp.conv2d_fwd(layer, x, prepared=True), pp.conv2d_fwd(other, x)
+    assert torch.equal(got, want) and not torch.equal(got, first)
+
+
+@pytest.mark.parametrize("dtype,shape", SHAPES)
+def test_first_prepared_call_in_a_graph(dtype, shape):
+    layer, x = _pair(3300, dtype, shape)
+    print("prepared, first call recorded", dtype, shape, flush=True)
+    layer.prepare()
+    out = torch.empty_like(pp.conv2d_fwd(layer, x))
+    layer.scratch.clear()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pp.conv2d_fwd(layer, x, out=out, prepared=True)
+    eager = pp.conv2d_fwd(layer, x, prepared=True)   # before the graph has run
+    want = pp.conv2d_fwd(layer, x)
+    assert torch.equal(eager, want)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        assert torch.equal(pp.conv2d_fwd(layer, x, prepared=True), want)
