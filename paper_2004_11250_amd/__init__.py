@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 import numpy as np
 
@@ -345,14 +346,18 @@ class PackedLayer:
         for k, v in state.items():
             setattr(self, k, v)
 
-    def _out_size(self, h, w):
-        """out_size of this layer, from its description alone."""
-        i = self.info
-        hn = h + 2 * i["pad"] - 2 * i["dilation"] - 1
-        wn = w + 2 * i["pad"] - 2 * i["dilation"] - 1
-        if h < 1 or w < 1 or hn < 0 or wn < 0:
-            return out_size(self.h_blob, h, w)   # raises the library's error
-        return hn // i["stride"] + 1, wn // i["stride"] + 1
+    def _shape(self, h, w):
+        """(c_out, c_in, h_out, w_out) for an h x w input, from the blob's own
+        header on every call, as the library reads it: a blob may be rebound
+        or rewritten in place."""
+        if self._h_blob.nbytes >= 28:
+            magic, _, c_out, c_in, stride, pad, dil = struct.unpack_from("<7I", self._h_blob)
+            hn, wn = h + 2 * pad - 2 * dil - 1, w + 2 * pad - 2 * dil - 1
+            if magic == 0x314B5050 and 1 <= stride <= 2 and pad <= 16 and 1 <= dil <= 2 and min(h, w) >= 1 and min(hn, wn) >= 0:
+                return c_out, c_in, hn // stride + 1, wn // stride + 1
+        ho, wo = out_size(self.h_blob, h, w)   # anything else: the library's answer, or its error
+        i = blob_info(self.h_blob)
+        return i["c_out"], i["c_in"], ho, wo
 
     def _workspace(self, n, h, w, act_dtype) -> int:
         """conv2d_workspace of this layer (asked every call: forced plans and
@@ -396,9 +401,10 @@ def conv2d_fwd(layer: PackedLayer, x, relu=False, out=None, stream=None, workspa
     if c != layer.info["c_in"]:
         raise ValueError(f"x has {c} channels, the layer expects {layer.info['c_in']}")
     hc, wc = (2 * h, 2 * w) if upsample2 else (h, w)   # the conv's input size
-    ho, wo = layer._out_size(hc, wc)
+    c_out, c_in, ho, wo = layer._shape(hc, wc)
+    if c != c_in:
+        raise ValueError(f"x has {c} channels, the layer expects {c_in}")
     dt = _dtype_code(x)
-    c_out = layer.info["c_out"]
     if maxpool2:
         ho, wo = ho // 2, wo // 2
     if pixshuf2:

@@ -151,6 +151,29 @@ def test_copied_layer_calls_with_its_own_blob(lib, how):
     assert other._workspace(1, 14, 14, pp.PP_F32) == pp.conv2d_workspace(blob, 1, 14, 14, pp.PP_F32)
 
 
+@pytest.mark.parametrize("how", ["rebound", "in place"])
+def test_output_is_sized_by_the_blob_that_is_called(lib, how):
+    # (an output sized by another description than the blob's would be written past its end)
+    layer = pp.PackedLayer.__new__(pp.PackedLayer)   # (no device copy)
+    old, new = _blob(stride=2, pad=1), _blob(c_out=20, stride=1, pad=2, dil=1)
+    layer.h_blob, layer.info = old.copy(), pp.blob_info(old)
+    assert layer._shape(20, 31) == (12, 5, *pp.out_size(old, 20, 31))
+    if how == "rebound":
+        layer.h_blob = new
+    else:
+        new = old.copy()
+        new.view(np.uint32)[4] = 1        # stride
+        layer.h_blob[:] = new
+    assert layer._shape(20, 31) == (20 if how == "rebound" else 12, 5, *pp.out_size(new, 20, 31))
+    with pytest.raises(pp.PPError):
+        layer._shape(0, 31)
+    layer.h_blob = _blob(stride=3)
+    assert layer._shape(20, 31)[2:] == pp.out_size(layer.h_blob, 20, 31)
+    layer.h_blob = new[:20]
+    with pytest.raises(pp.PPError):
+        layer._shape(20, 31)
+
+
 def test_out_size(lib):
     for (s, p, d, h, w) in ((1, 1, 1, 32, 32), (2, 1, 1, 33, 20), (1, 2, 2, 10, 7), (2, 0, 1, 9, 9)):
         ho, wo = pp.out_size(_blob(stride=s, pad=p, dil=d), h, w)
