@@ -299,7 +299,7 @@ class PackedLayer:
         self.d_blob = torch.from_numpy(self.h_blob.copy()).to(device)
         if self.d_blob.data_ptr() % 256:
             raise RuntimeError("device blob allocation is not 256-byte aligned")
-        self.scratch = {}   # conv2d_fwd workspaces by input shape
+        self.scratch = {}   # conv2d_fwd workspaces by input shape and stream
         self.prepared = None   # matrix-core weights (prepare())
 
     def prepare(self, stream=None):
@@ -384,7 +384,7 @@ def conv2d_fwd(layer: PackedLayer, x, relu=False, out=None, stream=None, workspa
                accumulate=False, pixshuf2=False, upsample2=False, prepared=False):
     """pp_conv2d_fwd on torch tensors; returns y (allocated when out is None).
     workspace: "auto" (a scratch tensor of pp_conv2d_workspace bytes, kept on
-    the layer per input shape), None (no scratch) or a uint8 device tensor.
+    the layer per input shape and stream), None (no scratch) or a uint8 device tensor.
     maxpool2: store the 2 x 2 max pool of the activated output (PP_MAXPOOL2).
     accumulate: add the activated output to ``out`` in place (PP_ACCUMULATE;
     out is required).  pixshuf2: store through PixelShuffle(2)
@@ -418,17 +418,20 @@ def conv2d_fwd(layer: PackedLayer, x, relu=False, out=None, stream=None, workspa
         raise ValueError(f"out must be a contiguous {x.dtype} tensor of shape {shape}")
     flags = ((PP_RELU if relu else 0) | (PP_MAXPOOL2 if maxpool2 else 0) | (PP_ACCUMULATE if accumulate else 0) |
              (PP_PIXSHUF2 if pixshuf2 else 0) | (PP_UPSAMPLE2 if upsample2 else 0))
+    sp = _stream_ptr(stream)
     if prepared or (isinstance(workspace, str) and workspace == "auto"):
         nb = layer._scratch_bytes(n, h, w, dt, flags | PP_PREPARED) if prepared else layer._workspace(n, hc, wc, dt)
-        key = (n, hc, wc, dt, x.device.index)
-        workspace = layer.scratch.get(key)
-        if nb and (workspace is None or workspace.numel() < nb):
-            workspace = torch.empty(nb, dtype=torch.uint8, device=x.device)
-            layer.scratch[key] = workspace
-        if not nb:
-            workspace = None
+        workspace = None
+        if nb:
+            # one per stream (calls that share one have to be ordered), of that stream's memory
+            key = (n, hc, wc, dt, x.device.index, sp)
+            workspace = layer.scratch.get(key)
+            if workspace is None or workspace.numel() < nb:
+                with torch.cuda.stream(None if stream is None else torch.cuda.ExternalStream(sp, x.device)):
+                    workspace = torch.empty(nb, dtype=torch.uint8, device=x.device)
+                layer.scratch[key] = workspace
     ws_ptr, ws_bytes = (workspace.data_ptr(), workspace.numel()) if workspace is not None else (None, 0)
-    args = (x.data_ptr(), out.data_ptr(), n, h, w, dt, flags, ws_ptr, ws_bytes, _stream_ptr(stream))
+    args = (x.data_ptr(), out.data_ptr(), n, h, w, dt, flags, ws_ptr, ws_bytes, sp)
     if prepared:
         st = lib.pp_conv2d_fwd_prepared(layer._h_ptr, layer._h_blob.nbytes, layer.d_blob.data_ptr(),
                                         layer.prepared.data_ptr(), layer.prepared.numel(), *args)

@@ -81,3 +81,25 @@ def test_first_prepared_call_in_a_graph(dtype, shape):
         torch.cuda.synchronize()
         assert torch.equal(out, want)
         assert torch.equal(pp.conv2d_fwd(layer, x, prepared=True), want)
+
+
+@pytest.mark.parametrize("prepared", [False, True])
+@pytest.mark.parametrize("dtype,shape", [("f32", (1, 512, 512, 14, 14)), ("bf16", (2, 128, 256, 40, 40))])
+def test_two_streams_have_scratch_of_their_own(dtype, shape, prepared):
+    # a channel split's partial sums (or the expanded weights) of calls that overlap
+    layer, x = _pair(3600, dtype, shape)
+    print("two streams", dtype, shape, prepared, flush=True)
+    layer.prepare()
+    xs = [x, (x * 0.5 + 1).contiguous()]
+    want = [pp.conv2d_fwd(layer, v, prepared=prepared) for v in xs]
+    outs = [[torch.empty_like(want[0]) for _ in range(20)] for _ in xs]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in xs]
+    for k in range(20):
+        for v, o, s in zip(xs, outs, streams):
+            pp.conv2d_fwd(layer, v, out=o[k], prepared=prepared, stream=s)
+    torch.cuda.synchronize()
+    for w, o in zip(want, outs):
+        assert all(torch.equal(y, w) for y in o)
+    bufs = [b.data_ptr() for b in layer.scratch.values()]
+    assert len(set(bufs)) == len(bufs) and (not bufs or len(bufs) == 3)   # the current stream's and theirs
