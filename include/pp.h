@@ -284,8 +284,9 @@ pp_status pp_conv2d_fwd_prepared(const void* h_blob, size_t blob_bytes, const vo
  * kernels read them, which pp_conv2d_fwd otherwise re-derives from the blob
  * on every call, in up to two parts.  The matrix-core part (bf16 layers
  * with c_in a multiple of 32): the layer as the masked dense contraction of
- * Sec. 2's pruning structure, bf16 [c_out][9][c_in] in original filter
- * order, zeros for taps off a kernel's pattern and for pruned kernels, then
+ * Sec. 2's pruning structure, bf16 [c_out x 9 x c_in] in the order in which
+ * the matrix cores take their operands, +0 for taps off a kernel's pattern
+ * and for pruned kernels (a stored zero is -0), then
  * the fp32 bias.  The lean part (layers of the canonical library with pad =
  * dilation: stride and dilation 1 (fp32 or bf16), or stride 1 and dilation
  * 2, or stride 2 and dilation 1 (fp32)), from the next 256-byte boundary after
@@ -294,6 +295,8 @@ pp_status pp_conv2d_fwd_prepared(const void* h_blob, size_t blob_bytes, const vo
  * expanded, zeros for pruned slots, fp32 [ceil(c_out/8)][c_in][32] (bf16
  * weights widened, exact), which the lean kernel reads by scalar loads
  * instead of staging them through LDS.  The
+ * buffer's form belongs to this build of the library: another one may order
+ * it differently at the same size, so it is not kept in files.  The
  * weights never change, so a caller that keeps the buffer passes it as the
  * workspace of later calls with PP_PREPARED (or as pp_net_op.d_w of the
  * layer in pp_net_fwd), and the per-call expansion is skipped.  A call whose

@@ -338,13 +338,22 @@ class PackedLayer:
     def h_blob(self, blob):
         self._h_blob, self._h_ptr = blob, blob.ctypes.data
 
+    # A copy or a saved layer carries no workspaces, and says of prepared
+    # weights only that there were some: their form is the library's that
+    # wrote them, so the one that loads them writes its own.
     def __getstate__(self):
-        d = {k: v for k, v in self.__dict__.items() if k not in ("_h_blob", "_h_ptr")}
-        return {"h_blob": self._h_blob, **d}
+        d = {k: v for k, v in self.__dict__.items() if k not in ("_h_blob", "_h_ptr", "scratch", "prepared")}
+        return {"h_blob": self._h_blob, "prepared": self.__dict__.get("prepared") is not None, **d}
 
     def __setstate__(self, state):
+        had = state.get("prepared")   # (a tensor in layers saved before)
         for k, v in state.items():
-            setattr(self, k, v)
+            if k not in ("scratch", "prepared"):
+                setattr(self, k, v)
+        self.scratch, self.prepared = {}, None
+        if had is not None and had is not False and self.d_blob.is_cuda:
+            with _torch().cuda.device(self.d_blob.device):
+                self.prepare()
 
     def _shape(self, h, w):
         """(c_out, c_in, h_out, w_out) for an h x w input, from the blob's own

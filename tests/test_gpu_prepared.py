@@ -103,3 +103,29 @@ def test_two_streams_have_scratch_of_their_own(dtype, shape, prepared):
         assert all(torch.equal(y, w) for y in o)
     bufs = [b.data_ptr() for b in layer.scratch.values()]
     assert len(set(bufs)) == len(bufs) and (not bufs or len(bufs) == 3)   # the current stream's and theirs
+
+
+@pytest.mark.parametrize("how", ["deepcopy", "pickle", "saved by another build"])
+@pytest.mark.parametrize("dtype,shape", SHAPES[:3])
+def test_copied_and_saved_layers_prepare_their_own(dtype, shape, how):
+    import copy
+    import io
+    layer, x = _pair(3700, dtype, shape)
+    print("prepared layer", how, dtype, shape, flush=True)
+    layer.prepare()
+    want = pp.conv2d_fwd(layer, x, prepared=True)
+    if how == "deepcopy":
+        other = copy.deepcopy(layer)
+    else:
+        if how != "pickle":   # as whole attributes, the prepared bytes in another order
+            state = dict(h_blob=layer.h_blob, info=layer.info, d_blob=layer.d_blob, scratch={},
+                         prepared=layer.prepared.view(-1, 2).flip(0).reshape(-1).contiguous())
+            other = pp.PackedLayer.__new__(pp.PackedLayer)
+            other.__setstate__(state)
+        else:
+            buf = io.BytesIO()
+            torch.save(layer, buf)
+            buf.seek(0)
+            other = torch.load(buf, weights_only=False)
+    assert other.prepared.data_ptr() != layer.prepared.data_ptr()
+    assert torch.equal(pp.conv2d_fwd(other, x, prepared=True), want)
