@@ -66,13 +66,16 @@ bool recipe_compiled(int lib, int id) {
   return lib == kLibCanon8 || id == 0 || id == 3 || id == 6 || id == 8 || id == 12 || id == 13;
 }
 
+// (a plan query has no x or y: the call plans again with its own)
+static bool aligned(const void* q, uintptr_t bytes) { return reinterpret_cast<uintptr_t>(q) % bytes == 0; }
+
 // a recipe that can run this layer: compiled for the library, fits in LDS,
 // (wave-pipeline kernel) compiled for the layer's padding (pad = dilation),
 // and (register-pipelined tilings) fp32 with the canonical library
 static bool recipe_usable(int id, const ConvParams& p, int lib, bool bf16) {
   if (!recipe_compiled(lib, id) || !recipe_fits(id, p.stride, p.dil, bf16, lib)) return false;
   if (is_lean_recipe(id)) {
-    if (bf16 && (p.w % 2 != 0 || (p.flags & (PP_UPSAMPLE2 | PP_PIXSHUF2)))) return false;
+    if (bf16 && (p.w % 2 != 0 || !aligned(p.x, 4) || (p.flags & (PP_UPSAMPLE2 | PP_PIXSHUF2)))) return false;
     if ((p.dil != 1 || p.stride != 1) && (p.flags & PP_UPSAMPLE2)) return false;
     return p.pad == p.dil && (!lean_v4(id) || (p.w % (bf16 ? 8 : 4) == 0 && !(p.flags & PP_UPSAMPLE2)));
   }
@@ -82,10 +85,9 @@ static bool recipe_usable(int id, const ConvParams& p, int lib, bool bf16) {
 
 bool gen_usable(int id, const ConvParams& p, bool bf16) {
   if (p.stride != 1 || p.dil != 1 || p.pad != 1 || (p.flags & ~static_cast<uint32_t>(PP_RELU))) return false;
-  if (bf16 && p.w % 2) return false;   // (its staging moves whole dwords)
+  if (bf16 && (p.w % 2 || !aligned(p.x, 4))) return false;   // (its staging moves whole dwords)
   const bool v4 = id == 66 || id == 68;
-  // (a plan query has no x: its launch checks the address)
-  return !v4 || (p.w % (bf16 ? 8 : 4) == 0 && reinterpret_cast<uintptr_t>(p.x) % 16 == 0);
+  return !v4 || (p.w % (bf16 ? 8 : 4) == 0 && aligned(p.x, 16));
 }
 
 static int env_recipe() {
@@ -253,10 +255,11 @@ ConvPlan plan_conv(const ConvParams& p, int lib, bool bf16, bool allow_split, bo
   // (64 -> 3 at 1080 x 1920: bf16 111 us, 228 on the wave kernel; fp32 138
   // against 172 there, 800 x 1280 60 against 82, 540 x 960 42 against 41.
   // fp32 only with every kernel kept: a pruned one's zero taps would meet
-  // infinities here, which the wave kernel never reads.)
+  // infinities here, which the wave kernel never reads; and only where its
+  // 16-byte loads and stores are aligned.)
   if (few_any && lib == kLibDense9 && forced < 0 &&
       (bf16 || (p.n == 1 && p.c_out <= 4 && static_cast<long>(p.h) * p.w >= 960L * 1024 &&
-                p.n_wt == 9u * static_cast<uint32_t>(p.c_in) * p.c_out)))
+                p.n_wt == 9u * static_cast<uint32_t>(p.c_in) * p.c_out && aligned(p.x, 16) && aligned(p.y, 16))))
     return few;
   // (dilation 2 = pad 2, or stride 2: fp32 only)
   const bool lean_layer = lib == kLibCanon8 && p.pad == p.dil &&

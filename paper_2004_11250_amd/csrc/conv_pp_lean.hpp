@@ -570,7 +570,9 @@ __global__ __launch_bounds__(WS * 64) void pp_conv3x3_lean_kernel(LeanParams a) 
   float* __restrict__ y = static_cast<float*>(a.y) + yoff;
   uint16_t* __restrict__ yb = static_cast<uint16_t*>(a.y) + yoff;   // bf16 output
   const int oxl = ox0 + lx * CC;
-  const bool vec = (CC % 4 == 0) && (a.wo % 4 == 0);
+  // 4 floats, or two bf16 outputs, per store where rows and y allow it
+  const bool vec = BF ? a.wo % 2 == 0 && reinterpret_cast<uintptr_t>(a.y) % 4 == 0
+                      : CC % 4 == 0 && a.wo % 4 == 0 && reinterpret_cast<uintptr_t>(a.y) % 16 == 0;
   // a row r of slot s: finish (bias, activation, store through perm) or,
   // under a channel split, store the partial sums to this split's block
   constexpr int BLK = 8 * R * CC * 64;
@@ -595,9 +597,9 @@ __global__ __launch_bounds__(WS * 64) void pp_conv3x3_lean_kernel(LeanParams a) 
     if constexpr (BF) {
       // one rounding to bf16 (PP_ACCUMULATE: the stored residual plus the
       // rounded activated value, rounded again); CC (even) outputs as dword
-      // pairs when the row and the lane's first column are even
+      // pairs when rows start on dwords (the lane's first column is even)
       uint16_t* row = yb + (static_cast<size_t>(o) * a.ho + oy) * a.wo;
-      if (a.wo % 2 == 0 && oxl + CC <= static_cast<int>(a.wo)) {
+      if (vec && oxl + CC <= static_cast<int>(a.wo)) {
 #pragma unroll
         for (int qq = 0; qq < CC; qq += 2) {
           uint32_t* pr = reinterpret_cast<uint32_t*>(row + oxl + qq);

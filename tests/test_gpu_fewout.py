@@ -149,3 +149,24 @@ def test_fewout_super_resolution_output_layer(dtype, monkeypatch):
         keep_hi = a1 if hi == h else min(a1, hi - lo - 1)
         check(y[:, :, lo + a0:lo + keep_hi], ref[:, :, a0:keep_hi], bound[:, :, a0:keep_hi], dtype,
               f"fewout sr rows {r0} {dtype}")
+
+
+@pytest.mark.parametrize("which", ["x", "y", "both"])
+def test_large_fp32_image_from_any_address(which):
+    # the few-output kernel's 16-byte loads and stores; tensors on a 4-byte
+    # boundary stay on the wave kernel.  Both sum in fp32: within the
+    # tolerance of each other.
+    n, c_out, c_in, h, w = 1, 3, 8, 960, 1024
+    L = workloads.random_layer(2900, c_out, c_in, lib=workloads.DENSE9, keep=1.0)
+    layer = pp.PackedLayer.from_weights(L["w"], L["b"], L["pid"], L["conn"], np.array(workloads.DENSE9, np.uint16))
+    size = pp.PackedLayer.from_weights(np.abs(L["w"]), np.abs(L["b"]), L["pid"], L["conn"], np.array(workloads.DENSE9, np.uint16))
+    assert pp.conv2d_recipe(layer.h_blob, n, h, w, pp.PP_F32) == 61
+    x = torch.from_numpy(workloads.random_input(2900, (n, c_in, h, w))).cuda()
+    print("fp32 image", which, (n, c_out, c_in, h, w), flush=True)
+    want, bound = pp.conv2d_fwd(layer, x), pp.conv2d_fwd(size, x.abs())
+    out = torch.empty(want.numel() + 1, device="cuda")[1:].view(want.shape) if which != "x" else torch.empty_like(want)
+    if which != "y":
+        x = torch.cat([x.new_zeros(1), x.reshape(-1)])[1:].view(x.shape)
+    out.fill_(float("nan"))
+    got = pp.conv2d_fwd(layer, x, out=out)
+    assert torch.all((got - want).abs() <= 2e-4 * bound)

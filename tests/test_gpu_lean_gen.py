@@ -76,3 +76,44 @@ def test_planned_and_unaligned(monkeypatch):
     off = torch.empty(x.numel() + 1, device="cuda")[1:].view(x.shape)   # 4-byte aligned: 4-byte staging, same sums
     off.copy_(x)
     assert torch.equal(pp.conv2d_fwd(layer, off), y)
+
+
+def _offset(t):
+    """a copy of t that starts one element past an aligned address"""
+    v = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")[1:].view(t.shape)
+    v.copy_(t)
+    return v
+
+
+@pytest.mark.parametrize("c_out,c_in,h,w,kind", [
+    (16, 32, 72, 72, "column"),      # the mask-testing tilings: 16-byte and 4-byte staging, large and small maps
+    (13, 33, 71, 70, "mixed"),
+    (24, 17, 24, 32, "wide"),
+    (24, 24, 19, 38, "column"),
+    (24, 48, 64, 64, "canon"),       # the lean kernel's own library
+    (24, 48, 100, 90, "canon"),
+])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("which", ["x", "y", "both"])
+def test_tensors_that_start_on_one_element(c_out, c_in, h, w, kind, dtype, which, monkeypatch):
+    # bf16 tensors on a 2-byte boundary, fp32 ones on a 4-byte boundary
+    monkeypatch.delenv("PP_RECIPE", raising=False)
+    wd = pp.PP_BF16 if dtype == "bf16" else pp.PP_F32
+    L = workloads.random_layer(2300, c_out, c_in) if kind == "canon" else _params(kind, 2300, c_out, c_in)
+    layer = pp.PackedLayer.from_weights(L["w"], L["b"], L["pid"], L["conn"], L["lib"], wdtype=wd)
+    x = workloads.random_input(2300, (2, c_in, h, w))
+    wt = L["w"]
+    if dtype == "bf16":
+        x, wt = obf16.round_f32(x), obf16.round_f32(wt)
+    args = (x, wt, L["b"], L["pid"], L["conn"], L["lib"])
+    ref, bound = oconv.conv3x3_pruned(*args, 1, 1, 1, True), oconv.conv3x3_bound(*args, 1, 1, 1)
+    xd = torch.from_numpy(x).cuda().to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    print("one element past", kind, dtype, which, (c_out, c_in, h, w), "plan", pp.conv2d_plan(layer.h_blob, 2, h, w, wd), flush=True)
+    out = torch.full((2, c_out, h, w), float("nan"), dtype=xd.dtype, device="cuda")
+    if which != "y":
+        xd = _offset(xd)
+    if which != "x":
+        out = _offset(out)
+    y = pp.conv2d_fwd(layer, xd, relu=True, out=out)
+    assert torch.isfinite(y).all()
+    check(y.float().cpu().numpy().astype(np.float64), ref, bound, dtype, f"one element past {kind} {which}")
