@@ -333,3 +333,24 @@ def test_mfma_64_channel_blocks(case, monkeypatch):
     y = _host(pp.conv2d_fwd(layer, _dev(x), relu=True))
     ref, bound = _oracle(L, x, 1, d, d, True)
     check(y, ref, bound, "bf16", f"mfma 64-channel blocks {case}")
+
+
+@pytest.mark.parametrize("mode", ["plain", "add", "pshuf2"])
+@pytest.mark.parametrize("w", [22, 21])
+def test_mfma_stores_from_any_address(mode, w, monkeypatch):
+    # an output that starts on an odd 2-byte element: the same values
+    monkeypatch.setenv("PP_RECIPE", str(MFMA))
+    n, c_out, c_in, h = 2, 72, 32, 15
+    L, layer = _layer(1800, c_out, c_in, "canon8", 0.5, 1, 1, 1)
+    x = _dev(workloads.random_input(1800, (n, c_in, h, w)))
+    _say("mfma store at an odd element", mode, (n, c_out, c_in, h, w))
+    kw = dict(accumulate=mode == "add", pixshuf2=mode == "pshuf2")
+    shape = (n, c_out // 4, 2 * h, 2 * w) if mode == "pshuf2" else (n, c_out, h, w)
+    r = _dev(workloads.random_input(1801, shape))
+    want = pp.conv2d_fwd(layer, x, out=r.clone(), **kw)
+    buf = torch.zeros(r.numel() + 3, dtype=r.dtype, device="cuda")
+    off = buf[1:-2].view(shape)
+    off.copy_(r)
+    assert off.data_ptr() % 4 == 2
+    assert torch.equal(pp.conv2d_fwd(layer, x, out=off, **kw), want)
+    assert not buf[0] and not buf[-2:].any()   # nothing beside it
