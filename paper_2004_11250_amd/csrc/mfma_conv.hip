@@ -24,7 +24,6 @@
 
 #include <algorithm>
 #include <cstdint>
-#include <type_traits>
 
 #include "conv_pp_kernel.hpp"
 
@@ -374,43 +373,29 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
     }
     return cvt_bf16x2(v0, v1);
   };
-  const bool y4 = reinterpret_cast<uintptr_t>(a.y) % 4 == 0;
-  if (a.flags & PP_PIXSHUF2) {
+  const bool shuf = (a.flags & PP_PIXSHUF2) != 0, y4 = reinterpret_cast<uintptr_t>(a.y) % 4 == 0;
+  if (shuf && y4) {
     // PixelShuffle(2): filters o, o + 1 (o even; accumulators r, r + 1)
     // land in adjacent columns 2 ex, 2 ex + 1 of one output row: one
-    // 4-byte store per pair (c_out is a multiple of 4; two 2-byte stores
-    // into a y that starts between dwords)
-    auto shuffle = [&](auto dwords) __attribute__((always_inline)) {
+    // 4-byte store per pair (c_out is a multiple of 4)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int ey = oy0 + prow + j * M::RPB;
-        if (ey >= a.ho || ex >= a.wo) continue;
-        const uint32_t voff = (half4 * static_cast<uint32_t>(plane) + (2u * ey) * 2u * a.wo + 2u * ex) * 2u;
+    for (int j = 0; j < TN; ++j) {
+      const int ey = oy0 + prow + j * M::RPB;
+      if (ey >= a.ho || ex >= a.wo) continue;
+      const uint32_t voff = (half4 * static_cast<uint32_t>(plane) + (2u * ey) * 2u * a.wo + 2u * ex) * 2u;
 #pragma unroll
-        for (int i = 0; i < MB; ++i)
+      for (int i = 0; i < MB; ++i)
 #pragma unroll
-          for (int r = 0; r < 16; r += 2) {
-            const int os = ob + 32 * i + 8 * (r >> 2);   // multiple of 8
-            uint8_t* row = reinterpret_cast<uint8_t*>(y + static_cast<size_t>(os) * plane + (r & 2) * a.wo);
-            if (os + static_cast<int>(half4) >= a.c_out) continue;
-            const uint32_t u = act2(i, j, r);
-            if constexpr (decltype(dwords)::value) {
-              *reinterpret_cast<uint32_t*>(row + voff) = u;
-            } else {
-              reinterpret_cast<uint16_t*>(row + voff)[0] = static_cast<uint16_t>(u);
-              reinterpret_cast<uint16_t*>(row + voff)[1] = static_cast<uint16_t>(u >> 16);
-            }
-          }
-      }
-    };
-    if (y4)
-      shuffle(std::true_type{});
-    else
-      shuffle(std::false_type{});
+        for (int r = 0; r < 16; r += 2) {
+          const int os = ob + 32 * i + 8 * (r >> 2);   // multiple of 8
+          uint8_t* row = reinterpret_cast<uint8_t*>(y + static_cast<size_t>(os) * plane + (r & 2) * a.wo);
+          if (os + static_cast<int>(half4) < a.c_out) *reinterpret_cast<uint32_t*>(row + voff) = act2(i, j, r);
+        }
+    }
     return;
   }
   const bool accum = (a.flags & PP_ACCUMULATE) != 0;
-  if (a.wo % 2 == 0 && y4) {
+  if (!shuf && a.wo % 2 == 0 && y4) {
     // columns in pairs: an even lane stores filter o of its and its
     // neighbour's pixel, the neighbour filter o + 1 of both (4-byte stores)
     const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
@@ -447,11 +432,14 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
     }
     return;
   }
+  // odd widths and a y that starts between dwords: 2-byte stores (shuffled:
+  // filters o, o + 1 in adjacent columns, as above)
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     const int ey = oy0 + prow + j * M::RPB;
     if (ey >= a.ho || ex >= a.wo) continue;
-    const uint32_t voff = (half4 * static_cast<uint32_t>(plane) + static_cast<uint32_t>(ey) * a.wo + ex) * 2u;
+    const uint32_t voff = (half4 * static_cast<uint32_t>(plane) +
+                           (shuf ? 4u * ey * a.wo + 2u * ex : static_cast<uint32_t>(ey) * a.wo + ex)) * 2u;
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
@@ -461,7 +449,8 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
         for (int k = 0; k < 2; ++k) {
           const int os = ob + 32 * i + 8 * (r >> 2) + (r & 3) + k;
           if (os + static_cast<int>(half4) >= a.c_out) break;
-          uint16_t* d = reinterpret_cast<uint16_t*>(reinterpret_cast<uint8_t*>(y + static_cast<size_t>(os) * plane) + voff);
+          const size_t at = shuf ? static_cast<size_t>(os & ~7) * plane + (r & 2) * a.wo + k : static_cast<size_t>(os) * plane;
+          uint16_t* d = reinterpret_cast<uint16_t*>(reinterpret_cast<uint8_t*>(y + at) + voff);
           const uint32_t b = k ? u >> 16 : u & 0xFFFFu;
           *d = static_cast<uint16_t>(accum ? cvt_bf16x2(bf16_val(*d) + bf16_val(b), 0.0f) : b);
         }
