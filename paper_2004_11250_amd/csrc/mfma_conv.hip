@@ -95,6 +95,32 @@ __global__ __launch_bounds__(256) void pp_mfma_expand_kernel(ConvParams a, uint1
   if (c == 0) bo[o] = reinterpret_cast<const float*>(a.blob + a.off_bias)[gs];
 }
 
+// Pairs of bf16 for the NaN repair (see pp_mfma_conv_kernel): per half, 1 for
+// a non-finite value (huge) or for a weight that is there (bits other than
+// +0), the sign of an infinity (of any weight but zero and NaN), and the
+// value with 1 of its sign in the place of an infinity or NaN.
+template <class F>
+__device__ __forceinline__ uint32_t halves(uint32_t u, F f) {
+  return f(u & 0xFFFFu) | f(u >> 16) << 16;
+}
+__device__ __forceinline__ uint32_t one_of_sign(uint32_t h) { return (h & 0x8000u) | 0x3F80u; }
+__device__ __forceinline__ bool is_huge(uint32_t h) { return (h & 0x7F80u) == 0x7F80u; }
+__device__ __forceinline__ uint32_t count_huge(uint32_t u) {
+  return halves(u, [](uint32_t h) { return is_huge(h) ? 0x3F80u : 0u; });
+}
+__device__ __forceinline__ uint32_t sign_inf(uint32_t u) {
+  return halves(u, [](uint32_t h) { return (h & 0x7FFFu) == 0x7F80u ? one_of_sign(h) : 0u; });
+}
+__device__ __forceinline__ uint32_t without_huge(uint32_t u) {
+  return halves(u, [](uint32_t h) { return is_huge(h) ? one_of_sign(h) : h; });
+}
+__device__ __forceinline__ uint32_t count_kept(uint32_t u) {
+  return halves(u, [](uint32_t h) { return h ? 0x3F80u : 0u; });
+}
+__device__ __forceinline__ uint32_t sign_weight(uint32_t u) {
+  return halves(u, [](uint32_t h) { return (h & 0x7FFFu) - 1u < 0x7F80u ? one_of_sign(h) : 0u; });
+}
+
 // lgkmcnt(0), then the workgroup barrier: LDS traffic is complete, global
 // loads stay in flight across it
 __device__ __forceinline__ void lds_barrier() {
@@ -309,10 +335,20 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
     lds_barrier();
   }
 
+  // where the lane's accumulators lie, worked out anew (held over the loop they would cost it registers)
+  const int ln = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  const int brow = wn * TN * M::RPB + (ln & 31) / M::TW, bcol = (ln & 31) % M::TW;
+
   // A pruned tap's zero weight times an infinity of the input is NaN, where the
-  // vector kernels never read that tap: outputs that came out NaN are summed
-  // again over the taps that are there.  Found by one FMA per accumulator pair
-  // (NaN stays; a false alarm only costs the look), 0.5 % of a 128 x 256 tile.
+  // vector kernels never read that tap.  Outputs that came out NaN (found by one
+  // FMA per accumulator pair: NaN stays, a false alarm only costs the look; 0.5 %
+  // of a 128 x 256 tile) are contracted again, a wave's 32 x 32 block at a time
+  // with its operands straight from memory: first how many products of taps that
+  // are there are infinite or NaN, and the signs of the infinite ones; then, where
+  // that leaves it open, the sum with those inputs out of it.  A last channel of
+  // NaN, us against the call without it: 512 -> 512 at 28 x 28 259 (27), 64 -> 256
+  // at 540 x 960 1984 (198), 64 -> 64 at 270 x 480 143 (17): about ten times,
+  // whatever the input (the loads' latency), and nothing held over the loop above.
   float probe = 0.0f;
 #pragma unroll
   for (int i = 0; i < MB; ++i)
@@ -321,48 +357,103 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
 #pragma unroll
       for (int r = 0; r < 16; r += 2) probe = __builtin_fmaf(acc[i][j][r], acc[i][j][r + 1], probe);
   if (__any(probe != probe)) {
-    const uint16_t* xi = static_cast<const uint16_t*>(a.x) + static_cast<size_t>(img) * a.c_in * hw;
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int oy = oy0 + prow + j * M::RPB, ox = ox0 + pcol;
-        uint32_t bad = 0;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) bad |= acc[i][j][r] != acc[i][j][r] ? 1u << r : 0u;
-        if (oy >= a.ho || ox >= a.wo) bad = 0;
 #pragma unroll 1
-        while (bad) {
-          const int r = __builtin_ctz(bad);
-          bad &= bad - 1;
-          const int o = mtile * M::BM + (wm * MB + i) * 32 + 8 * (r >> 2) + (lane >> 5) * 4 + (r & 3);
-          if (o >= a.c_out) continue;
-          const int rows = min(32, a.c_out - (o & ~31));
-          const uint16_t* wp = am + static_cast<size_t>(o >> 5) * 32 * 9 * a.c_in + (o & 31) * 8;
-          float sum = 0.0f;
-#pragma unroll 1
-          for (int e = 0; e < 9 * a.c_in && sum == sum; ++e) {
-            const int c = e / 9, t = e % 9;
-            const uint32_t wt = wp[static_cast<size_t>((c >> 4) * 18 + t * 2 + ((c >> 3) & 1)) * rows * 8 + (c & 7)];
-            const int gy = oy * S - a.pad + t / 3 * D, gx = ox * S - a.pad + t % 3 * D;
-            if (wt == 0 || gy < 0 || gy >= a.h || gx < 0 || gx >= a.w) continue;
-            const size_t el = up ? static_cast<size_t>(gy >> 1) * wsd + (gx >> 1) : static_cast<size_t>(gy) * wsd + gx;
-            sum = __builtin_fmaf(bf16_val(wt), bf16_val(xi[static_cast<size_t>(c) * hw + el]), sum);
-          }
+    for (int b = 0; b < MB * TN; ++b) {
+      uint32_t bad = 0;   // bit r: accumulator r of block b is NaN
 #pragma unroll
-          for (int k = 0; k < 16; ++k) acc[i][j][k] = k == r ? sum : acc[i][j][k];
+      for (int k = 0; k < MB * TN; ++k)
+        if (b == k) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) bad |= acc[k / TN][k % TN][r] != acc[k / TN][k % TN][r] ? 1u << r : 0u;
         }
+      const int oy = oy0 + brow + b % TN * M::RPB, ox = ox0 + bcol;
+      if (!__any(bad)) continue;
+      const int mb = mtile * (M::BM / 32) + wm * MB + b / TN;
+      const int rows = min(32, a.c_out - 32 * mb);
+      const uint32_t ao = (ln & 31) < rows
+                              ? static_cast<uint32_t>(mb) * 32u * 18u * a.c_in + ((ln >> 5) * rows + (ln & 31)) * 16u
+                              : kOut;
+      const uint32_t as = rows > 0 ? 32u * rows : 0u;
+      // op(weights, inputs) for every 16-deep k-step of the block, the loads of as
+      // many channel blocks at a time as the registers hold beside acc, and where
+      // they hold all three sums in one walk
+      constexpr int RU = CB == 64 ? 4 : 2;
+      constexpr bool kOnce = CB == 64;
+      auto steps = [&](auto op) __attribute__((always_inline)) {
+#pragma unroll 1
+        for (int t = 0; t < 9; ++t) {
+          const int gy = oy * S - a.pad + t / 3 * D, gx = ox * S - a.pad + t % 3 * D;
+          const bool ok = gy >= 0 && gy < a.h && gx >= 0 && gx < a.w;
+          const uint32_t el = up ? static_cast<uint32_t>(gy >> 1) * wsd + (gx >> 1) : static_cast<uint32_t>(gy) * wsd + gx;
+          const uint32_t xo = ok ? (static_cast<uint32_t>(img) * a.c_in * hw + 8u * (ln >> 5) * hw + el) * 2u : kOut;
+#pragma unroll 1
+          for (uint32_t c = 0; c < static_cast<uint32_t>(a.c_in); c += 16 * RU) {
+            u32x4v wt[RU], xv[RU];
+#pragma unroll
+            for (int q = 0; q < RU; ++q) {
+              wt[q] = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(
+                                                     arsrc, ao, static_cast<int>(((c >> 4) + q) * 9u * as + t * as), 0));
+#pragma unroll
+              for (int k = 0; k < 4; ++k) {
+                const uint32_t at = (c + 16 * q + 2 * k) * hw * 2u;
+                const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b16(xrsrc, xo, static_cast<int>(at), 0);
+                const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b16(xrsrc, xo, static_cast<int>(at + hw * 2u), 0);
+                xv[q][k] = (lo & 0xFFFFu) | hi << 16;
+              }
+            }
+#pragma unroll
+            for (int q = 0; q < RU; ++q) op(wt[q], xv[q]);
+          }
+        }
+      };
+      auto each = [](u32x4v v, auto f) { return __builtin_bit_cast(bf16x8, (u32x4v{f(v[0]), f(v[1]), f(v[2]), f(v[3])})); };
+      // n products, d of them +inf less those -inf (all of one sign only if n = |d|); sum: without those inputs
+      f32x16 n = f32x16{}, d = f32x16{}, sum = f32x16{};
+      auto count = [&](u32x4v w, u32x4v x) __attribute__((always_inline)) {
+        n = __builtin_amdgcn_mfma_f32_32x32x16_bf16(each(w, count_kept), each(x, count_huge), n, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(each(w, sign_weight), each(x, sign_inf), d, 0, 0, 0);
+      };
+      auto add = [&](u32x4v w, u32x4v x) __attribute__((always_inline)) {
+        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), each(x, without_huge), sum, 0, 0, 0);
+      };
+      if constexpr (kOnce) {
+        steps([&](u32x4v w, u32x4v x) __attribute__((always_inline)) {
+          count(w, x);
+          add(w, x);
+        });
+      } else {
+        steps(count);
       }
+      uint32_t plus = 0, minus = 0;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        plus |= n[r] + d[r] != 0.0f ? 1u << r : 0u;
+        minus |= n[r] - d[r] != 0.0f ? 1u << r : 0u;
+      }
+      if (!kOnce && __any(bad & ~(plus & minus))) steps(add);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        if ((plus >> r) & 1u) sum[r] += __builtin_inff();
+        if ((minus >> r) & 1u) sum[r] -= __builtin_inff();
+      }
+#pragma unroll
+      for (int k = 0; k < MB * TN; ++k)
+        if (b == k) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            acc[k / TN][k % TN][r] = (bad >> r) & 1u ? sum[r] : acc[k / TN][k % TN][r];
+        }
+    }
   }
 
   // accumulator r of block (i, j), lane l, is C[8 (r / 4) + 4 (l / 32) + r % 4][l % 32] of the block.
   // A row's address is a wave-uniform base (filter 8 (r / 4) + r % 4) plus a
   // 32-bit lane offset (4 filters for the upper half of the wave, and the pixel).
   const bool relu = (a.flags & PP_RELU) != 0;
-  const int ex = ox0 + pcol;
+  const int ex = ox0 + bcol;
   const size_t plane = static_cast<size_t>(a.ho) * a.wo;
   uint16_t* __restrict__ y = static_cast<uint16_t*>(a.y) + static_cast<size_t>(img) * a.c_out * plane;
-  const uint32_t half4 = (lane >> 5) * 4, odd = lane & 1;
+  const uint32_t half4 = (ln >> 5) * 4, odd = ln & 1;
   const int ob = mtile * M::BM + wm * MB * 32;   // the wave's first filter
   auto act2 = [&](int i, int j, int r) __attribute__((always_inline)) -> uint32_t {   // rows r, r + 1, in bf16
     const int ol = (wm * MB + i) * 32 + 8 * (r >> 2) + half4 + (r & 3);
@@ -380,7 +471,7 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
     // 4-byte store per pair (c_out is a multiple of 4)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const int ey = oy0 + prow + j * M::RPB;
+      const int ey = oy0 + brow + j * M::RPB;
       if (ey >= a.ho || ex >= a.wo) continue;
       const uint32_t voff = (half4 * static_cast<uint32_t>(plane) + (2u * ey) * 2u * a.wo + 2u * ex) * 2u;
 #pragma unroll
@@ -401,7 +492,7 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
     const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const int ey = oy0 + prow + j * M::RPB;
+      const int ey = oy0 + brow + j * M::RPB;
       const bool valid = ey < a.ho && ex < a.wo;
       const uint32_t voff = ((half4 + odd) * static_cast<uint32_t>(plane) + static_cast<uint32_t>(ey) * a.wo + ex - odd) * 2u;
 #pragma unroll
@@ -436,7 +527,7 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
   // filters o, o + 1 in adjacent columns, as above)
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
-    const int ey = oy0 + prow + j * M::RPB;
+    const int ey = oy0 + brow + j * M::RPB;
     if (ey >= a.ho || ex >= a.wo) continue;
     const uint32_t voff = (half4 * static_cast<uint32_t>(plane) +
                            (shuf ? 4u * ey * a.wo + 2u * ex : static_cast<uint32_t>(ey) * a.wo + ex)) * 2u;

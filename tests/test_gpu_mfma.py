@@ -354,3 +354,73 @@ def test_mfma_stores_from_any_address(mode, w, monkeypatch):
     assert off.data_ptr() % 4 == 2
     assert torch.equal(pp.conv2d_fwd(layer, x, out=off, **kw), want)
     assert not buf[0] and not buf[-2:].any()   # nothing beside it
+
+
+def _same_as_vector(layer, x, monkeypatch):
+    """(output, the channel-chunk kernel's): equal where that is not finite, else a bf16 ulp apart at most"""
+    n, _, h, w = x.shape
+    monkeypatch.setenv("PP_RECIPE", "64")
+    assert pp.conv2d_recipe(layer.h_blob, n, h, w, pp.PP_BF16) == MFMA
+    y = pp.conv2d_fwd(layer, x).float()
+    monkeypatch.setenv("PP_RECIPE", "13")
+    assert pp.conv2d_recipe(layer.h_blob, n, h, w, pp.PP_BF16) == 13
+    ref = pp.conv2d_fwd(layer, x, workspace=None).float()
+    fin = torch.isfinite(ref)
+    assert torch.equal(y[~fin].nan_to_num(nan=7.0), ref[~fin].nan_to_num(nan=7.0))
+    assert torch.all((y[fin] - ref[fin]).abs() <= 2 ** -7 * ref[fin].abs() + 1e-5)
+    return y
+
+
+@pytest.mark.parametrize("c_out,c_in,h,w,s,d", [
+    (64, 64, 20, 34, 1, 1), (40, 32, 13, 21, 2, 1), (136, 64, 17, 23, 1, 2), (256, 32, 96, 320, 1, 1),
+    (64, 32, 199, 512, 1, 1),
+])
+@pytest.mark.parametrize("what", ["nan channel", "inf everywhere", "-inf and positive weights", "inf weight", "random"])
+def test_mfma_non_finite_inputs(what, c_out, c_in, h, w, s, d, monkeypatch):
+    L = workloads.random_layer(1900, c_out, c_in, keep=0.4)
+    if what == "-inf and positive weights":
+        L["w"] = np.abs(L["w"])
+    if what == "inf weight":
+        L["w"][1, 2], L["w"][3, 4], L["w"][5, 6] = np.inf, -np.inf, np.nan
+    layer = pp.PackedLayer.from_weights(L["w"], L["b"], L["pid"], L["conn"], L["lib"], s, d, d, pp.PP_BF16)
+    x = _dev(workloads.random_input(1900, (1, c_in, h, w), 0.25, 1.0))
+    if what == "nan channel":
+        x[0, c_in - 1] = float("nan")
+    elif what == "inf everywhere":
+        x[:] = float("inf")
+    elif what == "-inf and positive weights":
+        x[:] = float("-inf")
+    else:
+        g = np.random.default_rng(1900)
+        for v in ("inf", "-inf", "nan"):
+            for _ in range(4):
+                x[0, g.integers(c_in), g.integers(h), g.integers(w)] = float(v)
+    _say("mfma non-finite", what, (c_out, c_in, h, w, s, d))
+    y = _same_as_vector(layer, x, monkeypatch)
+    assert not torch.isfinite(y).all()
+
+
+def test_mfma_nan_channel_is_bounded_in_time(monkeypatch):
+    # a last channel of NaN: every output meets it or a pruned tap of it; at
+    # most some times the call without it (a walk over every output's kept
+    # taps in turn took thousands)
+    monkeypatch.setenv("PP_RECIPE", str(MFMA))
+    L, layer = _layer(1910, 512, 512, "canon8", 1 / 3, 1, 1, 1)
+    layer.prepare()
+    x = _dev(workloads.random_input(1910, (1, 512, 28, 28)))
+    bad = x.clone()
+    bad[:, 511] = float("nan")
+
+    def us(v):
+        pp.conv2d_fwd(layer, v, prepared=True)
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(20):
+            pp.conv2d_fwd(layer, v, prepared=True)
+        b.record()
+        torch.cuda.synchronize()
+        return a.elapsed_time(b) * 50
+
+    t, tb = us(x), us(bad)
+    _say("512 -> 512 at 28 x 28:", t, "us, with a NaN channel", tb)
+    assert tb < 30 * t
