@@ -343,8 +343,8 @@ pp_status pp_conv2d_scratch(const void* h_blob, size_t blob_bytes, int32_t n, in
  * (with_workspace != 0) or without a pp_conv2d_workspace()-sized workspace.
  * Informational: lets callers and tests see which compiled kernel runs: ids
  * below 40 are vector-ALU tilings, 64 the bf16 matrix-core form (the layer as
- * a zero-filled dense contraction on the matrix cores; needs the workspace,
- * c_in a multiple of 32 and no fused max pool).  The environment variables
+ * a zero-filled dense contraction on the matrix cores; needs the workspace
+ * and c_in a multiple of 32).  The environment variables
  * PP_RECIPE=<id> and PP_KSPLIT=<k> force a tiling (when it can run the layer)
  * and a split; otherwise the planner's choice is reported.  ksplit may be NULL.  Host-only.  Errors: as pp_conv2d_out_size,
  * PP_EINVAL (recipe NULL, act_dtype), PP_EUNSUPPORTED.

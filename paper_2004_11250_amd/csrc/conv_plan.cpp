@@ -237,7 +237,9 @@ ConvPlan plan_conv(const ConvParams& p, int lib, bool bf16, bool allow_split, bo
   const int forced = env_recipe();
   ConvPlan mfma;
   mfma.recipe = kRecipeMfma;
-  const bool mfma_ok = bf16 && allow_split && mfma_eligible(p);
+  // (a fused pool: for the layers that have one on the vector kernels)
+  const bool mfma_ok = bf16 && allow_split && mfma_eligible(p) &&
+                       !(pool && (no_lean || lib == kLibGeneric || p.pad != p.dil));
   if (forced == kRecipeMfma && mfma_ok) return mfma;
   ConvPlan cin;
   cin.recipe = kRecipeCin;

@@ -184,7 +184,7 @@ struct ConvPlan {
 
 // bf16 layers as a zero-filled dense contraction on the matrix cores
 // (mfma_conv.hip): the plan's recipe id, whether a layer can run so (c_in a
-// multiple of 32, no fused max pool, offsets within 32 bits), the scratch it
+// multiple of 32, offsets within 32 bits), the scratch it
 // needs (the expanded weights and bias) and its launch (p.part = scratch).
 constexpr int kRecipeMfma = 64;
 

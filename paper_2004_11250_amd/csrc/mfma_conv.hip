@@ -464,6 +464,44 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
     }
     return cvt_bf16x2(v0, v1);
   };
+  if (a.flags & PP_MAXPOOL2) {
+    // the 2 x 2 max of the values the plain store would write: columns of a
+    // window are neighbouring lanes, its rows two of the wave's pixel blocks
+    // (32 columns across) or lanes 16 apart (16 across).  The even lane of a
+    // window stores filter o, the odd one filter o + 1.
+    static_assert(M::TW == 32 ? TN % 2 == 0 : M::RPB == 2, "a wave holds whole windows");
+    const uint32_t pw = a.wo / 2, pplane = pw * (a.ho / 2u);
+    uint16_t* __restrict__ yp = static_cast<uint16_t*>(a.y) + static_cast<size_t>(img) * a.c_out * pplane;
+    auto max2 = [](uint32_t u, uint32_t v) __attribute__((always_inline)) -> uint32_t {
+      return __float_as_uint(fmaxf(bf16_val(u), bf16_val(v))) >> 16 | __float_as_uint(fmaxf(bf16_hi(u), bf16_hi(v)));
+    };
+    auto across = [&](uint32_t u) __attribute__((always_inline)) -> uint32_t {
+      return max2(u, __builtin_amdgcn_mov_dpp(u, 0xB1, 0xF, 0xF, true));   // lanes 1, 0, 3, 2 of each four
+    };
+#pragma unroll
+    for (int j = 0; j < TN; j += M::TW == 32 ? 2 : 1) {
+      const int ey = oy0 + brow + j * M::RPB;   // the window's first row, in the lanes that store
+      const bool valid = (M::TW == 32 || (ln & 16) == 0) && ey + 1 < a.ho && (ex | 1) < a.wo;
+      // (one lane pointer walking the filters: an address per row would take the scalar registers)
+      int o = ob + half4 + odd;
+      uint16_t* d = yp + static_cast<size_t>(o) * pplane + (static_cast<uint32_t>(ey) >> 1) * pw + (static_cast<uint32_t>(ex) >> 1);
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+          uint32_t v = across(act2(i, j, r));
+          if constexpr (M::TW == 32)
+            v = max2(v, across(act2(i, j + 1, r)));
+          else
+            v = max2(v, __shfl_xor(v, 16));
+          if (valid && o < a.c_out) *d = static_cast<uint16_t>(odd ? v >> 16 : v);
+          const int next = r & 2 ? 6 : 2;   // filters 0, 2, 8, 10, 16, ... of the block
+          o += next;
+          d += static_cast<size_t>(next) * pplane;
+        }
+    }
+    return;
+  }
   const bool shuf = (a.flags & PP_PIXSHUF2) != 0, y4 = reinterpret_cast<uintptr_t>(a.y) % 4 == 0;
   if (shuf && y4) {
     // PixelShuffle(2): filters o, o + 1 (o even; accumulators r, r + 1)
@@ -609,7 +647,6 @@ hipError_t launch_tiles(const ConvParams& p, const uint16_t* am, const float* bo
 
 bool mfma_eligible(const ConvParams& p) {
   if (p.c_in < 32 || p.c_in % 32 != 0 || p.c_out < 1) return false;   // (staged 32 channels at a time)
-  if (p.flags & PP_MAXPOOL2) return false;
   if (p.stride < 1 || p.stride > 2 || p.dil < 1 || p.dil > 2 || p.pad < 0) return false;
   const bool up = (p.flags & PP_UPSAMPLE2) != 0;
   if (up && (p.h % 2 || p.w % 2)) return false;

@@ -424,3 +424,27 @@ def test_mfma_nan_channel_is_bounded_in_time(monkeypatch):
     t, tb = us(x), us(bad)
     _say("512 -> 512 at 28 x 28:", t, "us, with a NaN channel", tb)
     assert tb < 30 * t
+
+
+@pytest.mark.parametrize("relu", [True, False])
+@pytest.mark.parametrize("case", range(len(TILES) + 3))
+def test_mfma_fused_pool(case, relu, monkeypatch):
+    # every tile's 2 x 2 max pool: bitwise the pool of the plain store, odd
+    # rows and columns dropped; upsampled input and an odd output address too
+    monkeypatch.setenv("PP_RECIPE", str(MFMA))
+    (s, d), (n, c_out, c_in, h, w) = (TILES + [((1, 1), (1, 65, 128, 2, 2)), ((2, 2), (2, 33, 32, 21, 44)),
+                                               ((1, 1), (1, 100, 128, 9, 17))])[case]
+    seed = 2000 + case
+    L, layer = _layer(seed, c_out, c_in, "canon8", 0.5, s, d, d)
+    x = _dev(workloads.random_input(seed, (n, c_in, h, w)))
+    _say("mfma fused pool", (s, d), (n, c_out, c_in, h, w), "seed", seed)
+    plain = pp.conv2d_fwd(layer, x, relu=relu)
+    want = torch.nn.functional.max_pool2d(plain.float(), 2).to(torch.bfloat16)
+    out = torch.full((want.numel() + 3,), 7.0, dtype=want.dtype, device="cuda")
+    got = pp.conv2d_fwd(layer, x, relu=relu, maxpool2=True, out=out[1:-2].view(want.shape))
+    assert torch.equal(got, want)
+    assert out[0] == 7 and torch.all(out[-2:] == 7)
+    if h % 2 == 0 and w % 2 == 0:
+        up = pp.conv2d_fwd(layer, x[:, :, :h // 2, :w // 2].contiguous(), relu=relu, maxpool2=True, upsample2=True)
+        big = x[:, :, :h // 2, :w // 2].repeat_interleave(2, 2).repeat_interleave(2, 3).contiguous()
+        assert torch.equal(up, pp.conv2d_fwd(layer, big, relu=relu, maxpool2=True))

@@ -198,6 +198,30 @@ def test_net_fused_equals_unfused(cfg, dtype):
     assert np.array_equal(y_net, _np(slots[1]))
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_vgg16_fused_pools_equal_unfused(dtype):
+    # every fused max pool, on the matrix cores or not, against the conv and
+    # the pool as calls of their own
+    spec = workloads.net_spec(2)
+    params = workloads.net_params(2)
+    ops = spec["ops"]
+    net = pp.Net(ops, params, dtype)
+    _, x = _input(2, dtype)
+    plan = net.launch_plan(*x.shape)
+    assert len(plan["fused"]) == 5
+    if dtype == "bf16":
+        assert any(plan["recipe"][i - 1] == 64 for i in plan["fused"])
+    _say("vgg16", dtype, "fused pools vs op by op")
+    y, slots, li = net.forward(x), {0: x}, 0
+    for op in ops:
+        if op["op"] == "conv3":
+            slots[op["dst"]] = pp.conv2d_fwd(net.pruned[li], slots[op["src"]], relu=op["relu"])
+            li += 1
+        else:
+            slots[op["dst"]] = pp.Net([dict(op, src=0, dst=1)], [{}], dtype).forward(slots[op["src"]].contiguous())
+    assert torch.equal(y, slots[1])
+
+
 def test_vgg16_net_graph_replays():
     # pp_net_fwd captured as a HIP graph: every replay, with eager work and
     # synchronisation between replays and a new input each time, equals the

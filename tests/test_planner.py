@@ -79,3 +79,17 @@ def test_matrix_core_choice_over_the_range(c_out, c_in, s, d, n, h, w, keep, mfm
     assert (pp.conv2d_recipe(b, n, h, w, pp.PP_BF16) == MFMA) is mfma
     # without scratch for the expansion: another plan, never a refusal
     assert pp.conv2d_recipe(b, n, h, w, pp.PP_BF16, with_workspace=False) not in (MFMA, -1)
+
+
+def test_fused_pool_runs_the_form_of_the_plain_conv():
+    # a network's fused pool gives bitwise the conv and the pool apart, so both run one form
+    conv = dict(op="conv3", src=0, dst=2, c_in=64, c_out=64, stride=1, pad=1, dil=1, lib="canon8")
+    for c_out, c_in, hw in ((64, 64, 224), (256, 256, 56), (64, 64, 40), (64, 48, 100)):
+        L = workloads.random_layer(16, c_out, c_in, keep=1 / 3)
+        ops = [dict(conv, c_in=c_in, c_out=c_out), dict(op="maxpool2", src=2, dst=1)]
+        plan = pp.net_plan(ops, [L, {}], 1, c_in, hw, hw, "bf16")
+        alone = pp.conv2d_recipe(_blob(16, c_out, c_in, pp.PP_BF16, keep=1 / 3), 1, hw, hw, pp.PP_BF16)
+        assert plan["fused"] == {1: "maxpool2"} and plan["recipe"][0] == alone, (c_out, c_in, hw)
+    other = [0x00F, 0x0B2, 0x1C8, 0x055, 0x113, 0x0A9]   # any other library: no fused pool, as on the vector kernels
+    L = workloads.random_layer(17, 64, 64, lib=np.array(other, np.uint16))
+    assert pp.net_plan([conv, dict(op="maxpool2", src=2, dst=1)], [L, {}], 1, 64, 224, 224, "bf16")["fused"] == {}
