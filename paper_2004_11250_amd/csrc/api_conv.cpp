@@ -186,6 +186,15 @@ bool conv_fusable(const BlobView& v, int32_t n, int32_t h, int32_t w, int32_t ac
   const bool bf = act_dtype == PP_BF16;
   const ConvPlan fused = plan_conv(p, lib, bf, with_scratch);
   if (fused.recipe < 0) return false;
+  // a pool, add or shuffle that would take a conv off the few-input or
+  // few-output kernel, neither of which takes one, stays unfused, for the
+  // reason below
+  {
+    ConvParams q = p;
+    q.flags = flags & PP_UPSAMPLE2;
+    const int alone = plan_conv(q, lib, bf, with_scratch).recipe;
+    if ((alone == kRecipeFewOut || alone == kRecipeCin) && fused.recipe != alone) return false;
+  }
   // an upsample or a pixel shuffle that would take a conv off the matrix cores
   // stays unfused, for the reason below
   if (bf && fused.recipe != kRecipeMfma && (flags & (PP_UPSAMPLE2 | PP_PIXSHUF2))) {

@@ -314,3 +314,18 @@ def test_trace_ranges_change_nothing(tmp_path):
     _say("traced VGG-16 frame in a child process")
     subprocess.run([sys.executable, "-c", code], env=env, cwd=root, check=True, timeout=300)
     assert np.array_equal(np.load(out), want)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("c_in,c_out,hw,op", [(16, 4, (960, 1024), "pshuf2"), (16, 4, (960, 1024), "maxpool2"),
+                                              (3, 16, (64, 72), "maxpool2"), (64, 4, (40, 64), "pshuf2")])
+def test_few_channel_conv_and_the_op_after_it(c_in, c_out, hw, op, dtype):
+    # in a net bitwise what the two calls give apart
+    L = workloads.random_layer(3800, c_out, c_in, lib=workloads.DENSE9, keep=1.0)
+    conv = dict(op="conv3", src=0, dst=2, c_in=c_in, c_out=c_out, stride=1, pad=1, dil=1, relu=False)
+    net = pp.Net([conv, dict(op=op, src=2, dst=1)], [L, {}], dtype)
+    x = torch.from_numpy(workloads.random_input(3800, (1, c_in, *hw))).cuda()
+    x = x.to(torch.bfloat16) if dtype == "bf16" else x
+    _say("few-channel conv and", op, (c_in, c_out, hw), dtype, net.launch_plan(*x.shape)["fused"])
+    y = pp.conv2d_fwd(net.pruned[0], x)
+    assert torch.equal(net.forward(x), pp.Net([dict(op=op, src=0, dst=1)], [{}], dtype).forward(y))

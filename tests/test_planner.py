@@ -93,3 +93,20 @@ def test_fused_pool_runs_the_form_of_the_plain_conv():
     other = [0x00F, 0x0B2, 0x1C8, 0x055, 0x113, 0x0A9]   # any other library: no fused pool, as on the vector kernels
     L = workloads.random_layer(17, 64, 64, lib=np.array(other, np.uint16))
     assert pp.net_plan([conv, dict(op="maxpool2", src=2, dst=1)], [L, {}], 1, 64, 224, 224, "bf16")["fused"] == {}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("op", ["maxpool2", "pshuf2"])
+def test_no_fusion_takes_a_conv_off_the_few_channel_kernels(op, dtype):
+    # (they take no fused op, and the kernel that does sums in another order)
+    def plan(c_in, c_out, hw, lib):
+        conv = dict(op="conv3", src=0, dst=2, c_in=c_in, c_out=c_out, stride=1, pad=1, dil=1)
+        L = workloads.random_layer(18, c_out, c_in, lib=lib, keep=1.0)
+        return pp.net_plan([conv, dict(op=op, src=2, dst=1)], [L, {}], 1, c_in, *hw, dtype)
+
+    assert plan(64, 4, (960, 1024), workloads.DENSE9)["fused"] == {}
+    assert plan(64, 4, (960, 1024), workloads.DENSE9)["recipe"][0] == 61
+    assert plan(3, 16, (64, 64), workloads.DENSE9)["fused"] == {}
+    # layers of the other kernels fuse as before
+    assert plan(64, 4, (64, 64), workloads.DENSE9)["fused"] == ({1: op} if dtype == "f32" else {})
+    assert plan(64, 16, (960, 1024), workloads.DENSE9)["fused"] == {1: op}
