@@ -319,9 +319,9 @@ pp_status pp_conv2d_prepare(const void* h_blob, size_t blob_bytes, const void* d
 
 /*
  * pp_conv2d_workspace -- device scratch bytes pp_conv2d_fwd can use for this
- * layer and input (0: it would not use any); h, w are the conv's input size
- * (for a PP_UPSAMPLE2 call the upsampled size 2h x 2w; a call with fused
- * flags needs no more than the plain call).  Host-only.  Errors: as
+ * layer and input (0: it would not use any), whichever fused flags it has;
+ * h, w are the conv's input size (for a PP_UPSAMPLE2 call the upsampled size
+ * 2h x 2w).  Host-only.  Errors: as
  * pp_conv2d_out_size, PP_EINVAL (bytes NULL, act_dtype), PP_EUNSUPPORTED.
  */
 pp_status pp_conv2d_workspace(const void* h_blob, size_t blob_bytes, int32_t n, int32_t h,

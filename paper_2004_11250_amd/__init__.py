@@ -392,7 +392,7 @@ class PackedLayer:
 def conv2d_fwd(layer: PackedLayer, x, relu=False, out=None, stream=None, workspace="auto", maxpool2=False,
                accumulate=False, pixshuf2=False, upsample2=False, prepared=False):
     """pp_conv2d_fwd on torch tensors; returns y (allocated when out is None).
-    workspace: "auto" (a scratch tensor of pp_conv2d_workspace bytes, kept on
+    workspace: "auto" (a scratch tensor of pp_conv2d_scratch bytes, kept on
     the layer per input shape and stream), None (no scratch) or a uint8 device tensor.
     maxpool2: store the 2 x 2 max pool of the activated output (PP_MAXPOOL2).
     accumulate: add the activated output to ``out`` in place (PP_ACCUMULATE;
@@ -429,13 +429,14 @@ def conv2d_fwd(layer: PackedLayer, x, relu=False, out=None, stream=None, workspa
              (PP_PIXSHUF2 if pixshuf2 else 0) | (PP_UPSAMPLE2 if upsample2 else 0))
     sp = _stream_ptr(stream)
     if prepared or (isinstance(workspace, str) and workspace == "auto"):
-        nb = layer._scratch_bytes(n, h, w, dt, flags | PP_PREPARED) if prepared else layer._workspace(n, hc, wc, dt)
+        nb = layer._scratch_bytes(n, h, w, dt, flags | PP_PREPARED if prepared else flags)
         workspace = None
         if nb:
-            # one per stream (calls that share one have to be ordered), of that stream's memory
-            key = (n, hc, wc, dt, x.device.index, sp)
+            # one per stream (calls that share one have to be ordered), of that stream's
+            # memory; none is replaced (a graph may hold it)
+            key = (n, hc, wc, dt, x.device.index, sp, nb)
             workspace = layer.scratch.get(key)
-            if workspace is None or workspace.numel() < nb:
+            if workspace is None:
                 with torch.cuda.stream(None if stream is None else torch.cuda.ExternalStream(sp, x.device)):
                     workspace = torch.empty(nb, dtype=torch.uint8, device=x.device)
                 layer.scratch[key] = workspace

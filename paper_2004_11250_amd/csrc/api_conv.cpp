@@ -3,6 +3,7 @@
 // Sec. 2; conv fused with bias and activation, Sec. 3).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <string>
 
@@ -343,7 +344,14 @@ extern "C" pp_status pp_conv2d_workspace(const void* h_blob, size_t blob_bytes, 
   int ho = 0, wo = 0;
   s = conv_check(v, n, h, w, act_dtype, &ho, &wo);
   if (s != PP_OK) return s;
-  *bytes = call_scratch_bytes(v, n, h, w, act_dtype, 0);
+  // the most that any fused op asks for: one the lean kernel does not take may
+  // go to the matrix cores where the plain conv needs no scratch
+  *bytes = 0;
+  for (uint32_t f : {0u, uint32_t{PP_MAXPOOL2}, uint32_t{PP_ACCUMULATE}, uint32_t{PP_PIXSHUF2}})
+    for (uint32_t up : {0u, uint32_t{PP_UPSAMPLE2}}) {
+      if (((f & PP_PIXSHUF2) && v.c_out % 4) || (up && (h % 2 || w % 2))) continue;
+      *bytes = std::max(*bytes, call_scratch_bytes(v, n, h, w, act_dtype, f | up));
+    }
   return PP_OK;
 }
 

@@ -54,12 +54,9 @@ extern "C" pp_status pp_conv2d_fwd_noalloc(const void* h_blob, size_t blob_bytes
   pp_status s = parse_blob(h_blob, blob_bytes, &v, /*full=*/false);
   if (s != PP_OK) return s;
   if (flags & PP_PREPARED) return fail(PP_EINVAL, "PP_PREPARED needs the prepared weights as a workspace");
-  // the scratch pp_conv2d_fwd would use with a pp_conv2d_workspace()-sized
-  // workspace (that call sizes a PP_UPSAMPLE2 conv by its upsampled input)
-  const bool up = (flags & PP_UPSAMPLE2) != 0;
-  if (up && (h < 1 || w < 1 || h > (1 << 29) || w > (1 << 29))) return fail(PP_EINVAL, "bad h, w");
+  // the scratch pp_conv2d_fwd would use with enough workspace
   size_t need = 0;
-  s = pp_conv2d_workspace(h_blob, blob_bytes, n, up ? 2 * h : h, up ? 2 * w : w, act_dtype, &need);
+  s = pp_conv2d_scratch(h_blob, blob_bytes, n, h, w, act_dtype, flags, &need);
   if (s != PP_OK) return s;
   if (need > kScratchBytes)
     return fail(PP_ESIZE, "the layer needs " + std::to_string(need) + " bytes of scratch, more than the " +

@@ -129,3 +129,24 @@ def test_copied_and_saved_layers_prepare_their_own(dtype, shape, how):
             other = torch.load(buf, weights_only=False)
     assert other.prepared.data_ptr() != layer.prepared.data_ptr()
     assert torch.equal(pp.conv2d_fwd(other, x, prepared=True), want)
+
+
+@pytest.mark.parametrize("mode", ["pixshuf2", "upsample2"])
+def test_fused_call_takes_one_form_prepared_or_not(mode):
+    # lean alone (no scratch), on the matrix cores with the op fused: the same
+    # bits with the weights expanded per call, prepared, and in the call
+    # without an allocation
+    layer, x = _pair(3900, "bf16", (1, 128, 128, 128, 128))
+    print("one form", mode, flush=True)
+    if mode == "upsample2":
+        x = x[:, :, :64, :64].contiguous()
+    h, w = x.shape[2:]
+    layer.prepare()
+    want = pp.conv2d_fwd(layer, x, prepared=True, **{mode: True})
+    assert torch.equal(pp.conv2d_fwd(layer, x, **{mode: True}), want)
+    out = torch.empty_like(want)
+    lib, flag = pp.load_library(), pp.PP_PIXSHUF2 if mode == "pixshuf2" else pp.PP_UPSAMPLE2
+    assert lib.pp_conv2d_fwd_noalloc(layer.h_blob.ctypes.data, layer.h_blob.nbytes, layer.d_blob.data_ptr(), x.data_ptr(),
+                                     out.data_ptr(), 1, h, w, pp.PP_BF16, flag, None) == pp.PP_OK
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)

@@ -110,3 +110,23 @@ def test_no_fusion_takes_a_conv_off_the_few_channel_kernels(op, dtype):
     # layers of the other kernels fuse as before
     assert plan(64, 4, (64, 64), workloads.DENSE9)["fused"] == ({1: op} if dtype == "f32" else {})
     assert plan(64, 16, (960, 1024), workloads.DENSE9)["fused"] == {1: op}
+
+
+@pytest.mark.parametrize("c_out,c_in", [(128, 128), (64, 256), (64, 64), (256, 64)])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_workspace_covers_every_fused_call(c_out, c_in, dtype):
+    import ctypes
+    lib = pp.load_library()
+    b = _blob(19, c_out, c_in, dtype, keep=1 / 3)
+    grown = 0
+    for h, w in ((14, 14), (28, 28), (40, 56), (56, 56), (128, 128), (120, 200)):
+        ws, plain = pp.conv2d_workspace(b, 1, h, w, dtype), 0
+        for flags in (0, pp.PP_MAXPOOL2, pp.PP_ACCUMULATE, pp.PP_PIXSHUF2, pp.PP_UPSAMPLE2, pp.PP_UPSAMPLE2 | pp.PP_PIXSHUF2):
+            up = 2 if flags & pp.PP_UPSAMPLE2 else 1
+            nb = ctypes.c_size_t(0)
+            assert lib.pp_conv2d_scratch(b.ctypes.data, b.nbytes, 1, h // up, w // up, dtype, flags, ctypes.byref(nb)) == pp.PP_OK
+            assert nb.value <= ws
+            plain = nb.value if not flags else plain
+        grown += ws > plain
+    if (c_out, c_in, dtype) == (128, 128, 1):
+        assert grown   # 128 x 128: lean alone, on the matrix cores with a shuffle
