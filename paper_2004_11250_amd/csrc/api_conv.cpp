@@ -61,6 +61,8 @@ ConvParams layer_params(const BlobView& v, int32_t n, int32_t h, int32_t w, int 
 
 ConvPlan plan_with_scratch(const ConvParams& p, int kind, bool bf16, size_t scratch_bytes, bool no_lean) {
   ConvPlan pl = plan_conv(p, kind, bf16, scratch_bytes > 0, no_lean);
+  if (pl.recipe == kRecipeMfma && split_bytes(pl, p) > scratch_bytes)   // no room for the weights: perhaps for a split
+    pl = plan_conv(p, kind, bf16, true, no_lean, /*no_mfma=*/true);
   if (split_bytes(pl, p) > scratch_bytes) pl = plan_conv(p, kind, bf16, false, no_lean);   // no room: no split
   return pl;
 }
@@ -239,6 +241,22 @@ static size_t call_scratch_bytes(const BlobView& v, int32_t n, int32_t h, int32_
     if (b > bytes) bytes = b;
   }
   return bytes;
+}
+
+bool conv_runs_small(const BlobView& v, int32_t n, int32_t h, int32_t w, int32_t act_dtype, uint32_t flags, size_t limit) {
+  const int up = flags & PP_UPSAMPLE2 ? 2 : 1;
+  int ho = 0, wo = 0;
+  if (conv_check(v, n, up * h, up * w, act_dtype, &ho, &wo) != PP_OK) return false;
+  const ConvParams p = layer_params(v, n, up * h, up * w, ho, wo);
+  const bool bf = act_dtype == PP_BF16;
+  auto fits = [&](int kind, bool no_lean) {
+    const ConvPlan pl = plan_conv(p, kind, bf, true, no_lean);
+    if (split_bytes(pl, p) <= limit) return true;
+    return pl.recipe == kRecipeMfma && vector_reach(p, kind, no_lean) &&
+           split_bytes(plan_conv(p, kind, bf, true, no_lean, /*no_mfma=*/true), p) <= limit;
+  };
+  const int lib = library_kind(v);
+  return fits(lib, false) && (lib != kLibGeneric || !jit_library4(v) || fits(kLibCanon8, true));
 }
 
 // launch parameters of one layer for an n x c_in x h x w input (device

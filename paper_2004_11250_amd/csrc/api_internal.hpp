@@ -58,4 +58,9 @@ const void* lean_prepared(const BlobView& v, const void* prepared);
 // conv's input size (with PP_UPSAMPLE2 the upsampled size)
 size_t conv_scratch_bytes(const BlobView& v, int32_t n, int32_t h, int32_t w, int32_t act_dtype, uint32_t flags = 0);
 
+// whether a layer whose call wants more than `limit` bytes of scratch for the
+// matrix-core form's weights runs with that much on the vector kernels
+// (h, w: the stored input size)
+bool conv_runs_small(const BlobView& v, int32_t n, int32_t h, int32_t w, int32_t act_dtype, uint32_t flags, size_t limit);
+
 }  // namespace pp

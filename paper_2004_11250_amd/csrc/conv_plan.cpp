@@ -219,7 +219,21 @@ static bool mfma_pays(const ConvParams& p, bool lean) {
   return t_mfma < t_vec && t_mfma + expand < 1.12 * t_vec;
 }
 
-ConvPlan plan_conv(const ConvParams& p, int lib, bool bf16, bool allow_split, bool no_lean) {
+// (the line is where this call's vector plans have always ended: callers that
+// cannot allocate rely on what lies inside it.  1024 -> 1024 and more, steps
+// and rates as in mfma_pays for a third of the kernels kept.)
+bool vector_reach(const ConvParams& p, int lib, bool no_lean) {
+  const double map = static_cast<double>(p.ho) * p.wo, pix = p.n * map;
+  const bool lean = lib == kLibCanon8 && p.pad == 1 && p.stride == 1 && p.dil == 1 && p.c_in > 8 && p.w % 2 == 0 && !no_lean;
+  const double rate = p.n == 1 && map >= 256.0 * 256.0 && map < 512.0 * 512.0 ? 1.25e12
+                      : (p.n > 1 ? pix >= 65536.0 : map >= 160.0 * 160.0) ? 1.0e12
+                      : (p.n > 1 || map >= 80.0 * 80.0)                 ? 1.5e12
+                                                                        : 1.1e12;
+  const double t = lean ? pix * p.c_in * p.n_groups / rate + 5e-6 : pix * p.n_wt * (p.stride == 2 ? 2.2 : 1.0) / 12e12 + 8e-6;
+  return t <= 0.169e-6 * p.c_in + 8e-6;
+}
+
+ConvPlan plan_conv(const ConvParams& p, int lib, bool bf16, bool allow_split, bool no_lean, bool no_mfma) {
   const bool pool = (p.flags & PP_MAXPOOL2) != 0;
   // epilogues of the wave-pipeline kernel only
   const bool fused = (p.flags & (PP_MAXPOOL2 | PP_ACCUMULATE | PP_PIXSHUF2 | PP_UPSAMPLE2)) != 0;
@@ -238,7 +252,7 @@ ConvPlan plan_conv(const ConvParams& p, int lib, bool bf16, bool allow_split, bo
   ConvPlan mfma;
   mfma.recipe = kRecipeMfma;
   // (a fused pool: for the layers that have one on the vector kernels)
-  const bool mfma_ok = bf16 && allow_split && mfma_eligible(p) &&
+  const bool mfma_ok = bf16 && allow_split && !no_mfma && mfma_eligible(p) &&
                        !(pool && (no_lean || lib == kLibGeneric || p.pad != p.dil));
   if (forced == kRecipeMfma && mfma_ok) return mfma;
   ConvPlan cin;

@@ -219,8 +219,15 @@ hipError_t launch_mfma_expand(const ConvParams& p, void* out, hipStream_t st);  
 // tilings, and recipe -1 means none can.  (p.h, p.w are the conv's input
 // size: the upsampled size with PP_UPSAMPLE2.)
 // no_lean: plan among the wave-pipeline tilings only (the run-time compiled
-// kernels of pp_jit_library exist for those)
-ConvPlan plan_conv(const ConvParams& p, int lib, bool bf16, bool allow_split, bool no_lean = false);
+// kernels of pp_jit_library exist for those); no_mfma: not the matrix-core
+// form (its weights do not fit the scratch)
+ConvPlan plan_conv(const ConvParams& p, int lib, bool bf16, bool allow_split, bool no_lean = false,
+                   bool no_mfma = false);
+
+// whether the vector kernels run a bf16 layer in at most about 0.17 us per
+// input channel and 8 us: where the allocation-free call, whose scratch
+// cannot hold the layer's expanded weights, still runs it
+bool vector_reach(const ConvParams& p, int lib, bool no_lean);
 // scratch bytes a plan needs (its partial-sum blocks, or the matrix-core
 // form's expanded weights); 0 for none
 size_t split_bytes(const ConvPlan& plan, const ConvParams& p);

@@ -58,10 +58,14 @@ extern "C" pp_status pp_conv2d_fwd_noalloc(const void* h_blob, size_t blob_bytes
   size_t need = 0;
   s = pp_conv2d_scratch(h_blob, blob_bytes, n, h, w, act_dtype, flags, &need);
   if (s != PP_OK) return s;
-  if (need > kScratchBytes)
-    return fail(PP_ESIZE, "the layer needs " + std::to_string(need) + " bytes of scratch, more than the " +
-                              std::to_string(kScratchBytes) + " the allocation-free call holds; use pp_conv2d_fwd " +
-                              "with a workspace");
+  if (need > kScratchBytes) {
+    // expanded weights past the array: the vector kernels, where they are not much slower
+    if (!conv_runs_small(v, n, h, w, act_dtype, flags, kScratchBytes))
+      return fail(PP_ESIZE, "the layer needs " + std::to_string(need) + " bytes of scratch, more than the " +
+                                std::to_string(kScratchBytes) + " the allocation-free call holds; use pp_conv2d_fwd " +
+                                "with a workspace");
+    need = kScratchBytes;
+  }
   void* sp = nullptr;
   if (need > 0) {
     s = scratch_address(&sp);

@@ -87,3 +87,29 @@ def test_noalloc_rejects_layers_beyond_the_scratch():
     assert b"scratch" in lib.pp_last_error()
     torch.cuda.synchronize()
     assert torch.count_nonzero(y).item() == 0   # nothing was enqueued
+
+
+@pytest.mark.parametrize("c_out,c_in,n,h,w,s,d", [
+    (1024, 1024, 1, 14, 14, 1, 1),    # a channel split beside it
+    (1024, 1024, 1, 28, 28, 1, 1),
+    (768, 2048, 2, 7, 66, 1, 1),
+    (1024, 1024, 1, 21, 13, 2, 1),    # the wave kernel
+    (512, 2048, 1, 9, 11, 1, 2),
+])
+def test_noalloc_runs_wide_layers_on_the_vector_kernels(c_out, c_in, n, h, w, s, d):
+    # expanded weights past the array: the plan that pp_conv2d_fwd makes with a workspace of the array's size
+    L = workloads.random_layer(3950, c_out, c_in, keep=0.3)
+    layer = pp.PackedLayer.from_weights(L["w"], L["b"], L["pid"], L["conn"], L["lib"], s, d, d, pp.PP_BF16)
+    x = torch.from_numpy(workloads.random_input(3950, (n, c_in, h, w))).cuda().to(torch.bfloat16)
+    ho, wo = pp.out_size(layer.h_blob, h, w)
+    nb = pp.conv2d_workspace(layer.h_blob, n, h, w, pp.PP_BF16)
+    _say("noalloc, wide layer", (c_out, c_in, n, h, w, s, d), "workspace", nb)
+    y = torch.full((n, c_out, ho, wo), float("nan"), dtype=x.dtype, device="cuda")
+    lib = pp.load_library()
+    assert lib.pp_conv2d_fwd_noalloc(layer.h_blob.ctypes.data, layer.h_blob.nbytes, layer.d_blob.data_ptr(), x.data_ptr(),
+                                     y.data_ptr(), n, h, w, pp.PP_BF16, pp.PP_RELU, None) == pp.PP_OK, lib.pp_last_error()
+    torch.cuda.synchronize()
+    small = torch.empty(LIMIT, dtype=torch.uint8, device="cuda")
+    assert torch.equal(y, pp.conv2d_fwd(layer, x, relu=True, workspace=small))
+    full = pp.conv2d_fwd(layer, x, relu=True).float()
+    assert torch.isfinite(y).all() and (y.float() - full).norm() <= 7e-3 * full.norm()
