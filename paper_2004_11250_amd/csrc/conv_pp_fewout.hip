@@ -16,9 +16,11 @@
 // per lane, weights read from LDS.  The columns beside a lane's four come from
 // its neighbours by DPP: loading them too asked the caches for every line
 // three times, and that, not memory, bound the kernel.  64 -> 3 at
-// 1080 x 1920: fp32 190 -> 144 us (3.9 TB/s), bf16 134 -> 111 us.  Even and odd
-// channels have sums of their own (fp32 error against 64 bits 2.7e-7 -> 1.8e-7
-// of the result, the wave kernel's 2.0e-7).
+// 1080 x 1920: fp32 170 us on the wave kernel, 135 here (4.1 TB/s); bf16 134
+// with the columns loaded, 111.  The sums are taken four channels at a time:
+// fp32 error against 64 bits there 1.0e-7 to 1.2e-7 of the result over three
+// seeds, 1.9e-7 to 2.3e-7 on the wave kernel (13 channels 8.5e-8 against
+// 1.0e-7); two chains over all the channels were as far off as that kernel.
 //
 // Tile: a wave covers 64 x 8 outputs (16 lanes across x 4 down, a 2 x 4
 // block per lane); a workgroup is 4 waves stacked vertically (64 x 32).
@@ -32,7 +34,8 @@ namespace pp {
 namespace kern {
 
 constexpr int kFewTW = 64, kFewTH = 32;   // workgroup tile (4 waves of 64 x 8)
-constexpr int kFewAhead = 2;               // channels in flight (even: odd and even ones have sums of their own)
+constexpr int kFewAhead = 2;               // channels in flight
+constexpr int kFewFold = 4;                // channels of a partial sum (a multiple of kFewAhead)
 constexpr int kFewLds = 60 * 1024;        // bytes of the expanded weight table at most
 
 template <int NF>
@@ -165,19 +168,30 @@ __global__ __launch_bounds__(256, NF == 8 ? 2 : NF == 4 ? 3 : 4) void pp_conv3x3
     }
   };
 
-  float acc[NF][2][4], acc1[NF][2][4];   // sums over the even and the odd channels
+  float acc[NF][2][4], part[NF][2][4];   // part: the sum over up to kFewFold channels, then added to acc
 #pragma unroll
   for (int s = 0; s < NF; ++s)
 #pragma unroll
     for (int r = 0; r < 2; ++r)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc[s][r][q] = acc1[s][r][q] = 0.0f;
+      for (int q = 0; q < 4; ++q) acc[s][r][q] = part[s][r][q] = 0.0f;
+  auto fold = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < NF; ++s)
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          acc[s][r][q] += part[s][r][q];
+          part[s][r][q] = 0.0f;
+        }
+  };
 
   // one channel: its FMAs, then its registers take the rows of the channel
   // kFewAhead further on (unconditionally: past the last channel that one's
   // again, so the loads are not in a branch the compiler would place after
   // the FMAs)
-  auto step = [&](int c, Rows& p, float (&acc)[NF][2][4]) __attribute__((always_inline)) {
+  auto step = [&](int c, Rows& p) __attribute__((always_inline)) {
     float pt[4][6];
     patch(p, pt);
     const float* wc = wtab + c * WPC;
@@ -191,7 +205,7 @@ __global__ __launch_bounds__(256, NF == 8 ? 2 : NF == 4 ? 3 : 4) void pp_conv3x3
 #pragma unroll
           for (int r = 0; r < 2; ++r)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) acc[s][r][q] = __builtin_fmaf(wv, pt[r + ky][q + kx], acc[s][r][q]);
+            for (int q = 0; q < 4; ++q) part[s][r][q] = __builtin_fmaf(wv, pt[r + ky][q + kx], part[s][r][q]);
         }
     load_rows(min(c + kFewAhead, a.c_in - 1), p);
     __builtin_amdgcn_sched_barrier(0);
@@ -200,19 +214,16 @@ __global__ __launch_bounds__(256, NF == 8 ? 2 : NF == 4 ? 3 : 4) void pp_conv3x3
 #pragma unroll
   for (int i = 0; i < kFewAhead; ++i) load_rows(min(i, a.c_in - 1), rows[i]);
 #pragma unroll 1
-  for (int c = 0; c + kFewAhead <= a.c_in; c += kFewAhead)
+  for (int c = 0; c + kFewAhead <= a.c_in; c += kFewAhead) {
 #pragma unroll
-    for (int i = 0; i < kFewAhead; ++i) step(c + i, rows[i], i & 1 ? acc1 : acc);
+    for (int i = 0; i < kFewAhead; ++i) step(c + i, rows[i]);
+    if (c % kFewFold == kFewFold - kFewAhead) fold();
+  }
   const int rest = a.c_in % kFewAhead;
 #pragma unroll
   for (int i = 0; i < kFewAhead - 1; ++i)
-    if (i < rest) step(a.c_in - rest + i, rows[i], i & 1 ? acc1 : acc);
-#pragma unroll
-  for (int s = 0; s < NF; ++s)
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) acc[s][r][q] += acc1[s][r][q];
+    if (i < rest) step(a.c_in - rest + i, rows[i]);
+  fold();
 
   // ---- epilogue: + bias, ReLU, store through perm (slot s of group 0)
   if (!lane_in) return;

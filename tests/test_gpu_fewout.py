@@ -170,3 +170,27 @@ def test_large_fp32_image_from_any_address(which):
     out.fill_(float("nan"))
     got = pp.conv2d_fwd(layer, x, out=out)
     assert torch.all((got - want).abs() <= 2e-4 * bound)
+
+
+@pytest.mark.parametrize("c_out,c_in", [(3, 64), (4, 96), (1, 64), (3, 13)])
+def test_large_fp32_image_error_against_64_bits(c_out, c_in):
+    # no further off than the wave kernel that these layers were taken from:
+    # over seeds 1.8e-7 to 2.9e-7 of the result there for 64 and 96 channels,
+    # 9.3e-8 to 1.07e-7 for 13; 1.0e-7 to 1.3e-7 and 8.4e-8 to 8.7e-8 here
+    h, w = 960, 1024
+    g = np.random.default_rng(c_in)
+    W = (g.standard_normal((c_out, c_in, 3, 3)) * np.sqrt(2 / (9 * c_in))).astype(np.float32)
+    b = (0.1 * g.standard_normal(c_out)).astype(np.float32)
+    layer = pp.PackedLayer.from_weights(W, b, np.zeros((c_out, c_in), np.uint8), np.ones((c_out, c_in), np.uint8),
+                                        np.array(workloads.DENSE9, np.uint16))
+    assert pp.conv2d_recipe(layer.h_blob, 1, h, w, pp.PP_F32) == 61
+    x = torch.from_numpy(np.maximum(g.standard_normal((1, c_in, h, w), dtype=np.float32), 0)).cuda()
+    print("fp32 image against 64 bits", c_out, c_in, flush=True)
+    y = pp.conv2d_fwd(layer, x).double()
+    ref = torch.from_numpy(b).double().cuda().view(1, c_out, 1, 1).expand(1, c_out, h, w).clone()
+    xp, wd = torch.nn.functional.pad(x.double(), (1, 1, 1, 1)), torch.from_numpy(W).double().cuda()
+    for ky in range(3):
+        for kx in range(3):
+            v = xp[0, :, ky:ky + h, kx:kx + w].reshape(c_in, h * w)
+            ref += (wd[:, :, ky, kx].contiguous() @ v).view(1, c_out, h, w)
+    assert float((y - ref).norm() / ref.norm()) < (1.6e-7 if c_in > 13 else 9.3e-8)
