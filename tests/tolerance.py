@@ -21,7 +21,7 @@ def check(y, y_ref, bound, dtype="f32", what=""):
     assert y.shape == y_ref.shape == bound.shape, (what, y.shape, y_ref.shape, bound.shape)
     err = np.abs(y - y_ref)
     lim = TOL[dtype] * bound
-    bad = err > lim
+    bad = ~(err <= lim)   # (a NaN is out of it)
     if np.any(bad):
         i = np.unravel_index(np.argmax(np.where(bad, err / np.maximum(lim, 1e-300), 0)), y.shape)
         raise AssertionError(f"{what}: {int(bad.sum())} of {y.size} outputs out of tolerance; worst at {i}: "
