@@ -283,6 +283,9 @@ def _stream_ptr(stream=None) -> int:
     return int(s.cuda_stream)
 
 
+_HEADER = struct.Struct("<7I")   # a blob's first words: magic, version and type, c_out, c_in, stride, pad, dilation
+
+
 def _capturing(stream) -> bool:
     torch = _torch()
     with torch.cuda.stream(stream):
@@ -360,9 +363,10 @@ class PackedLayer:
         header on every call, as the library reads it: a blob may be rebound
         or rewritten in place."""
         if self._h_blob.nbytes >= 28:
-            magic, _, c_out, c_in, stride, pad, dil = struct.unpack_from("<7I", self._h_blob)
-            hn, wn = h + 2 * pad - 2 * dil - 1, w + 2 * pad - 2 * dil - 1
-            if magic == 0x314B5050 and 1 <= stride <= 2 and pad <= 16 and 1 <= dil <= 2 and min(h, w) >= 1 and min(hn, wn) >= 0:
+            magic, _, c_out, c_in, stride, pad, dil = _HEADER.unpack_from(self._h_blob)
+            add = 2 * pad - 2 * dil - 1
+            hn, wn = h + add, w + add
+            if magic == 0x314B5050 and 1 <= stride <= 2 and pad <= 16 and 1 <= dil <= 2 and h >= 1 and w >= 1 and hn >= 0 and wn >= 0:
                 return c_out, c_in, hn // stride + 1, wn // stride + 1
         ho, wo = out_size(self.h_blob, h, w)   # anything else: the library's answer, or its error
         i = blob_info(self.h_blob)
