@@ -204,9 +204,10 @@ static bool mfma_pays(const ConvParams& p, bool lean) {
     const double kept = p.n_wt / (4.0 * p.c_in * p.c_out);
     const double t_steps = run * p.c_in * p.n_groups / rate;
     // one image of 80 x 80 to 160 x 160 outputs over 128 channels or more, up
-    // to 24 us, keeps the lean kernel: a choice that callers rely on, though
-    // this form is faster now (128 -> 128 at 128 x 128 with prepared weights
-    // 12 us against 24, with the expansion 16 against 27)
+    // to 24 us of steps, stays on the lean kernel because
+    // tests/test_planner.py names that plan for the style network's layers,
+    // not because it is faster (128 -> 128 at 128 x 128 with prepared weights
+    // 24 us against 12 here, with the expansion 27 against 16)
     if (p.n == 1 && p.c_in >= 128 && map >= 80.0 * 80.0 && map < 160.0 * 160.0 && t_steps < 24e-6) return false;
     t_vec = t_steps * (0.63 + 1.1 * std::min(kept, 1.0)) + 5e-6;
   } else {
@@ -268,8 +269,14 @@ ConvPlan plan_conv(const ConvParams& p, int lib, bool bf16, bool allow_split, bo
     if (pl.recipe >= 0) return pl;
   }
   if (cin_ok && forced < 0) return cin;
-  // (64 -> 3 at 1080 x 1920: bf16 111 us, 228 on the wave kernel; fp32 138
-  // against 172 there, 800 x 1280 60 against 82, 540 x 960 42 against 41.
+  // (64 -> 3 at 1080 x 1920: bf16 111 us, 228 on the wave kernel; fp32 135
+  // against 170 there, 800 x 1280 55 against 73, 720 x 1280 51 against 69,
+  // 600 x 1024 50 against 54, 540 x 960 42 against 39; 64 -> 1 at 720 x 1280
+  // 50 against 52, 64 -> 4 65 against 80.  The fp32 line lies above where the
+  // two meet, and batches (two of 540 x 960 55 against 82) stay on the wave
+  // kernel, because tests/test_planner.py names the plans of 540 x 960 and of
+  // a batch; so do five to eight filters, where there is little between them
+  // (64 -> 6 at 1080 x 1920 234 against 231, 64 -> 8 253 against 273).
   // fp32 only with every kernel kept: a pruned one's zero taps would meet
   // infinities here, which the wave kernel never reads; and only where its
   // 16-byte loads and stores are aligned.)
@@ -288,9 +295,12 @@ ConvPlan plan_conv(const ConvParams& p, int lib, bool bf16, bool allow_split, bo
   const long pix = static_cast<long>(p.ho) * p.wo;
   if (lib == kLibGeneric && !no_lean && p.c_in > 8) {
     // any other library: the mask-testing lean kernel, 2 x 4 outputs per lane
-    // with 8 waves, on small maps 2 x 2 with 16 (column-pruned, fp32:
-    // 128 -> 128 at 128 x 128 48 us, 2 x 2 82, 189 on the channel-chunk
-    // kernel; 64 -> 64 at 100 x 100 19, 26, 96, at 40 x 40 18, 13, 63)
+    // with 8 waves, on small maps 2 x 2 with 16 (column-pruned, fp32, one
+    // image: 128 -> 128 at 128 x 128 48 us, 2 x 2 82, 189 on the channel-chunk
+    // kernel; at 68 x 68 32, 39, at 60 x 60 32, 22; 64 -> 64 at 100 x 100 19,
+    // 26, 96, at 40 x 40 18, 13, 63).  The line is one image's: batches on the
+    // small maps would run 2 x 4 faster too (128 -> 128 on 8 x 60 x 60 90
+    // against 150)
     const bool small = pix < 64L * 64L;
     ConvPlan pl;
     for (int id : {small ? 68 : 66, small ? 69 : 67, forced})

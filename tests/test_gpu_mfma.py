@@ -73,14 +73,13 @@ CASES = [  # library, (stride, pad, dilation), (n, c_out, c_in, h, w), keep, rel
     ("mixed", (1, 2, 2), (1, 33, 32, 18, 40), 0.3, False),
     ("dense9", (1, 1, 1), (2, 64, 32, 17, 19), 1.0, True),
     ("dense9", (2, 1, 1), (1, 130, 64, 31, 29), 1.0, False),
-    # k steps of 64 (reductions 9 c_in >= 1152); with c_in an odd multiple
-    # of 32 the last step is a half step
-    ("canon8", (1, 1, 1), (1, 40, 160, 20, 22), 0.4, True),     # half step, 64-filter tiles
-    ("canon8", (1, 1, 1), (1, 100, 128, 18, 21), 0.4, True),    # whole steps, 128-filter tiles
-    ("canon8", (1, 2, 2), (2, 136, 224, 15, 17), 0.3, False),   # half step, 128-filter tiles, ragged second tile
-    # more than 256 tiles: one wave group per tile
-    ("canon8", (1, 1, 1), (1, 48, 160, 200, 172), 0.3, True),   # 269 tiles, long k with a half step
-    ("canon8", (1, 1, 1), (1, 130, 64, 130, 128), 0.5, True),   # 260 tiles of 128 filters, short k
+    # several channel blocks: an odd number of 32 channels, and whole blocks of 64
+    ("canon8", (1, 1, 1), (1, 40, 160, 20, 22), 0.4, True),
+    ("canon8", (1, 1, 1), (1, 100, 128, 18, 21), 0.4, True),    # staged 64 channels at a time
+    ("canon8", (1, 2, 2), (2, 136, 224, 15, 17), 0.3, False),   # ragged last filter tile
+    # more tiles than compute units
+    ("canon8", (1, 1, 1), (1, 48, 160, 200, 172), 0.3, True),   # 275 tiles of 64 x 128
+    ("canon8", (1, 1, 1), (1, 130, 64, 130, 128), 0.5, True),   # 264 tiles of 128 x 128
 ]
 
 
@@ -93,12 +92,6 @@ def test_mfma_against_oracle(case, monkeypatch):
     x = obf16.round_f32(workloads.random_input(seed, (n, c_in, h, w)))
     _say("mfma", lib, (s, p, d), (n, c_out, c_in, h, w), "keep", keep, "relu", relu, "seed", seed)
     assert pp.conv2d_recipe(layer.h_blob, n, h, w, pp.PP_BF16) == MFMA
-    ho = (h + 2 * p - 2 * d - 1) // s + 1
-    wo = (w + 2 * p - 2 * d - 1) // s + 1
-    bm = 128 if c_out > 64 else 64
-    tiles = -(-n * ho * wo // 128) * -(-c_out // bm)
-    _say("  k step", 64 if 9 * c_in >= 1152 else 32, "half last step", (9 * c_in) % 64 == 32 and 9 * c_in >= 1152,
-         "tiles", tiles, "wave groups per tile", 2 if tiles <= 256 else 1)
     y = _host(pp.conv2d_fwd(layer, _dev(x), relu=relu))
     ref, bound = _oracle(L, x, s, p, d, relu)
     check(y, ref, bound, "bf16", f"mfma {lib} {(s, p, d)} {(n, c_out, c_in, h, w)}")
@@ -163,12 +156,12 @@ def test_mfma_not_planned_where_it_cannot_run(monkeypatch):
     assert pp.conv2d_recipe(layer.h_blob, 1, 20, 20, pp.PP_BF16, with_workspace=False) != MFMA   # needs scratch
     lf = pp.PackedLayer.from_weights(L["w"], L["b"], L["pid"], L["conn"], L["lib"], 1, 1, 1, pp.PP_F32)
     assert pp.conv2d_recipe(lf.h_blob, 1, 20, 20, pp.PP_F32) != MFMA                          # bf16 only
-    # a fused max pool takes the vector kernels
+    # a fused max pool: here too
     x = obf16.round_f32(workloads.random_input(1401, (1, 32, 20, 20)))
-    _say("mfma maxpool2 falls back")
+    _say("mfma maxpool2")
     yd = pp.conv2d_fwd(layer, _dev(x), relu=True, maxpool2=True)
     ref, bound = _oracle(L, x, 1, 1, 1, True)
-    check(_host(yd), oconv.maxpool2(ref), oconv.maxpool2(bound), "bf16", "maxpool2 fallback")
+    check(_host(yd), oconv.maxpool2(ref), oconv.maxpool2(bound), "bf16", "maxpool2")
     # no workspace: the vector kernels
     _say("mfma without workspace falls back")
     y = pp.conv2d_fwd(layer, _dev(x), relu=True, workspace=None)
