@@ -157,7 +157,7 @@ struct MGeo {
 // touch LDS: every wave reads its own filters', so a k-step costs a unit's
 // cache 4 MB KB.  The 64 x 128 tile therefore takes one block of filters by
 // two of pixels per wave (with two by one, all four waves read the same
-// filters: bound by that cache at 43 of its 64 B per clock, also with four
+// filters: bound by that cache, also with four
 // times the waves; 512 -> 512 at 14 x 14 28.7 -> 22.3, 256 -> 256 at 56 x 56
 // 17.4 -> 14.0, 64 -> 64 at 224 x 224 12.6 -> 9.9, 512 -> 512 stride 2 at 32 x
 // 32 41.8 -> 36.4), its pixel operands read two k-steps ahead (3 % of those).
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; r += 2) probe = __builtin_fmaf(acc[i][j][r], acc[i][j][r + 1], probe);
-  if (__any(probe != probe)) {
+  if (__builtin_expect(__any(probe != probe), 0)) {
 #pragma unroll 1
     for (int b = 0; b < MB * TN; ++b) {
       uint32_t bad = 0;   // bit r: accumulator r of block b is NaN
@@ -466,7 +466,92 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
     }
     return cvt_bf16x2(v0, v1);
   };
-  if (a.flags & PP_MAXPOOL2) {
+  const bool shuf = (a.flags & PP_PIXSHUF2) != 0, y4 = reinterpret_cast<uintptr_t>(a.y) % 4 == 0;
+  const bool pool = (a.flags & PP_MAXPOOL2) != 0;
+  const bool accum = (a.flags & PP_ACCUMULATE) != 0;
+  // (the plain stores first: on the smallest grids a jump over the others costs 1 to 5 %)
+  if (__builtin_expect(!pool && !shuf && a.wo % 2 == 0 && y4, 1)) {
+    // columns in pairs: an even lane stores filter o of its and its
+    // neighbour's pixel, the neighbour filter o + 1 of both (4-byte stores)
+    const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int ey = oy0 + brow + j * M::RPB;
+      const bool valid = ey < a.ho && ex < a.wo;
+      const uint32_t voff = ((half4 + odd) * static_cast<uint32_t>(plane) + static_cast<uint32_t>(ey) * a.wo + ex - odd) * 2u;
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        auto at = [&](int r) __attribute__((always_inline)) {
+          return reinterpret_cast<uint32_t*>(
+              reinterpret_cast<uint8_t*>(y + static_cast<size_t>(ob + 32 * i + 8 * (r >> 2) + (r & 3)) * plane) + voff);
+        };
+        auto in = [&](int r) __attribute__((always_inline)) {
+          return valid && ob + 32 * i + 8 * (r >> 2) + (r & 3) + static_cast<int>(half4 + odd) < a.c_out;
+        };
+        uint32_t old[8];
+        if (accum) {
+#pragma unroll
+          for (int r = 0; r < 16; r += 2) old[r / 2] = in(r) ? *at(r) : 0u;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+          const uint32_t u = act2(i, j, r);
+          const uint32_t nb = __builtin_amdgcn_mov_dpp(u, 0xB1, 0xF, 0xF, true);   // lanes 1, 0, 3, 2 of each four
+          uint32_t t = __builtin_amdgcn_perm(nb, u, sel);
+          // PP_ACCUMULATE: y = y + act(...), the activated value rounded to bf16 first
+          if (accum)
+            t = cvt_bf16x2(bf16_val(old[r / 2]) + bf16_val(t), bf16_hi(old[r / 2]) + bf16_hi(t));
+          if (in(r)) *at(r) = t;
+        }
+      }
+    }
+    return;
+  }
+  if (__builtin_expect(!shuf && !pool, 1)) {
+    // odd widths and a y that starts between dwords: 2-byte stores
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int ey = oy0 + brow + j * M::RPB;
+      if (ey >= a.ho || ex >= a.wo) continue;
+      const uint32_t voff = (half4 * static_cast<uint32_t>(plane) + static_cast<uint32_t>(ey) * a.wo + ex) * 2u;
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+          const uint32_t u = act2(i, j, r);
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            const int os = ob + 32 * i + 8 * (r >> 2) + (r & 3) + k;
+            if (os + static_cast<int>(half4) >= a.c_out) break;
+            uint16_t* d = reinterpret_cast<uint16_t*>(reinterpret_cast<uint8_t*>(y + static_cast<size_t>(os) * plane) + voff);
+            const uint32_t b = k ? u >> 16 : u & 0xFFFFu;
+            *d = static_cast<uint16_t>(accum ? cvt_bf16x2(bf16_val(*d) + bf16_val(b), 0.0f) : b);
+          }
+        }
+    }
+    return;
+  }
+  if (shuf && y4) {
+    // PixelShuffle(2): filters o, o + 1 (o even; accumulators r, r + 1)
+    // land in adjacent columns 2 ex, 2 ex + 1 of one output row: one
+    // 4-byte store per pair (c_out is a multiple of 4)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int ey = oy0 + brow + j * M::RPB;
+      if (ey >= a.ho || ex >= a.wo) continue;
+      const uint32_t voff = (half4 * static_cast<uint32_t>(plane) + (2u * ey) * 2u * a.wo + 2u * ex) * 2u;
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+          const int os = ob + 32 * i + 8 * (r >> 2);   // multiple of 8
+          uint8_t* row = reinterpret_cast<uint8_t*>(y + static_cast<size_t>(os) * plane + (r & 2) * a.wo);
+          if (os + static_cast<int>(half4) < a.c_out) *reinterpret_cast<uint32_t*>(row + voff) = act2(i, j, r);
+        }
+    }
+    return;
+  }
+  if (pool) {
     // the 2 x 2 max of the values the plain store would write: columns of a
     // window are neighbouring lanes, its rows two of the wave's pixel blocks
     // (32 columns across) or lanes 16 apart (16 across).  The even lane of a
@@ -504,11 +589,8 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
     }
     return;
   }
-  const bool shuf = (a.flags & PP_PIXSHUF2) != 0, y4 = reinterpret_cast<uintptr_t>(a.y) % 4 == 0;
-  if (shuf && y4) {
-    // PixelShuffle(2): filters o, o + 1 (o even; accumulators r, r + 1)
-    // land in adjacent columns 2 ex, 2 ex + 1 of one output row: one
-    // 4-byte store per pair (c_out is a multiple of 4)
+  {
+    // the shuffle into a y that starts between dwords: two 2-byte stores
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int ey = oy0 + brow + j * M::RPB;
@@ -518,74 +600,15 @@ __global__ __launch_bounds__(256, 2) void pp_mfma_conv_kernel(ConvParams a, cons
       for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int r = 0; r < 16; r += 2) {
-          const int os = ob + 32 * i + 8 * (r >> 2);   // multiple of 8
-          uint8_t* row = reinterpret_cast<uint8_t*>(y + static_cast<size_t>(os) * plane + (r & 2) * a.wo);
-          if (os + static_cast<int>(half4) < a.c_out) *reinterpret_cast<uint32_t*>(row + voff) = act2(i, j, r);
-        }
-    }
-    return;
-  }
-  const bool accum = (a.flags & PP_ACCUMULATE) != 0;
-  if (!shuf && a.wo % 2 == 0 && y4) {
-    // columns in pairs: an even lane stores filter o of its and its
-    // neighbour's pixel, the neighbour filter o + 1 of both (4-byte stores)
-    const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int ey = oy0 + brow + j * M::RPB;
-      const bool valid = ey < a.ho && ex < a.wo;
-      const uint32_t voff = ((half4 + odd) * static_cast<uint32_t>(plane) + static_cast<uint32_t>(ey) * a.wo + ex - odd) * 2u;
-#pragma unroll
-      for (int i = 0; i < MB; ++i) {
-        auto at = [&](int r) __attribute__((always_inline)) {
-          return reinterpret_cast<uint32_t*>(
-              reinterpret_cast<uint8_t*>(y + static_cast<size_t>(ob + 32 * i + 8 * (r >> 2) + (r & 3)) * plane) + voff);
-        };
-        auto in = [&](int r) __attribute__((always_inline)) {
-          return valid && ob + 32 * i + 8 * (r >> 2) + (r & 3) + static_cast<int>(half4 + odd) < a.c_out;
-        };
-        uint32_t old[8];
-        if (accum) {
-#pragma unroll
-          for (int r = 0; r < 16; r += 2) old[r / 2] = in(r) ? *at(r) : 0u;
-        }
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
+          const int os = ob + 32 * i + 8 * (r >> 2);
+          uint16_t* d = reinterpret_cast<uint16_t*>(
+              reinterpret_cast<uint8_t*>(y + static_cast<size_t>(os) * plane + (r & 2) * a.wo) + voff);
+          if (os + static_cast<int>(half4) >= a.c_out) continue;
           const uint32_t u = act2(i, j, r);
-          const uint32_t nb = __builtin_amdgcn_mov_dpp(u, 0xB1, 0xF, 0xF, true);   // lanes 1, 0, 3, 2 of each four
-          uint32_t t = __builtin_amdgcn_perm(nb, u, sel);
-          // PP_ACCUMULATE: y = y + act(...), the activated value rounded to bf16 first
-          if (accum)
-            t = cvt_bf16x2(bf16_val(old[r / 2]) + bf16_val(t), bf16_hi(old[r / 2]) + bf16_hi(t));
-          if (in(r)) *at(r) = t;
+          d[0] = static_cast<uint16_t>(u);
+          d[1] = static_cast<uint16_t>(u >> 16);
         }
-      }
     }
-    return;
-  }
-  // odd widths and a y that starts between dwords: 2-byte stores (shuffled:
-  // filters o, o + 1 in adjacent columns, as above)
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int ey = oy0 + brow + j * M::RPB;
-    if (ey >= a.ho || ex >= a.wo) continue;
-    const uint32_t voff = (half4 * static_cast<uint32_t>(plane) +
-                           (shuf ? 4u * ey * a.wo + 2u * ex : static_cast<uint32_t>(ey) * a.wo + ex)) * 2u;
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; r += 2) {
-        const uint32_t u = act2(i, j, r);
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const int os = ob + 32 * i + 8 * (r >> 2) + (r & 3) + k;
-          if (os + static_cast<int>(half4) >= a.c_out) break;
-          const size_t at = shuf ? static_cast<size_t>(os & ~7) * plane + (r & 2) * a.wo + k : static_cast<size_t>(os) * plane;
-          uint16_t* d = reinterpret_cast<uint16_t*>(reinterpret_cast<uint8_t*>(y + at) + voff);
-          const uint32_t b = k ? u >> 16 : u & 0xFFFFu;
-          *d = static_cast<uint16_t>(accum ? cvt_bf16x2(bf16_val(*d) + bf16_val(b), 0.0f) : b);
-        }
-      }
   }
 }
 
