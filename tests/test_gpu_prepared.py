@@ -150,3 +150,28 @@ def test_fused_call_takes_one_form_prepared_or_not(mode):
                                      out.data_ptr(), 1, h, w, pp.PP_BF16, flag, None) == pp.PP_OK
     torch.cuda.synchronize()
     assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("dtype,shape", SHAPES)
+def test_prepared_weights_at_the_head_of_a_workspace(dtype, shape):
+    # pp_conv2d_fwd with PP_PREPARED: the weights, then scratch from the next
+    # 256-byte boundary; and without that scratch
+    layer, x = _pair(4000, dtype, shape)
+    n, c_out, c_in, h, w = shape
+    wd = layer.info["wdtype"]
+    print("prepared head", dtype, shape, flush=True)
+    head = layer.prepare()
+    tail = pp.conv2d_workspace(layer.h_blob, n, h, w, wd)
+    size = -(-head.numel() // 256) * 256 + tail
+    ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")
+    ws[:head.numel()] = head
+    lib = pp.load_library()
+    for nbytes, want in ((size, pp.conv2d_fwd(layer, x, relu=True, prepared=True)),
+                         (head.numel(), None if tail else pp.conv2d_fwd(layer, x, relu=True, workspace=None))):
+        y = torch.full((n, c_out, h, w), float("nan"), dtype=x.dtype, device="cuda")
+        st = lib.pp_conv2d_fwd(layer.h_blob.ctypes.data, layer.h_blob.nbytes, layer.d_blob.data_ptr(), x.data_ptr(),
+                               y.data_ptr(), n, h, w, wd, pp.PP_RELU | pp.PP_PREPARED, ws.data_ptr(), nbytes, None)
+        assert st == pp.PP_OK, lib.pp_last_error()
+        torch.cuda.synchronize()
+        assert torch.isfinite(y).all() and (want is None or torch.equal(y, want))
+    assert torch.equal(ws[:head.numel()], head)   # read only
