@@ -213,15 +213,18 @@ pp_status pp_blob_info(const void* h_blob, size_t bytes, pp_layer_desc* d,
  *                       activated value rounded to act_dtype before the add:
  *                       bitwise what a separate add of the stored output
  *                       gives; canonical or all-ones library with pad =
- *                       dilation, else PP_EUNSUPPORTED), PP_PIXSHUF2 (y is
+ *                       dilation, and any library and padding where a bf16
+ *                       layer runs on the matrix cores (plan id 64 of
+ *                       pp_conv2d_recipe, with its workspace or prepared
+ *                       weights), else PP_EUNSUPPORTED), PP_PIXSHUF2 (y is
  *                       [n][c_out/4][2 h_out][2 w_out], y[c][2i+a][2j+b] =
  *                       act(conv + bias)[4c+2a+b][i][j]; c_out a multiple of
- *                       4, else PP_EINVAL; same libraries as PP_ACCUMULATE);
+ *                       4, else PP_EINVAL; same layers as PP_ACCUMULATE);
  *                       at most one of PP_MAXPOOL2, PP_ACCUMULATE and
  *                       PP_PIXSHUF2, else PP_EINVAL; PP_UPSAMPLE2 (the conv
  *                       reads x [n][c_in][h][w] as its nearest x2 upsampling
  *                       [n][c_in][2h][2w]: h_out, w_out are those of a 2h x 2w
- *                       input; same libraries as PP_ACCUMULATE; combines with
+ *                       input; same layers as PP_ACCUMULATE; combines with
  *                       the others)
  *   workspace, ws_bytes optional device scratch (NULL, 0 for none), 256-byte
  *                       aligned.  With pp_conv2d_workspace() bytes the
